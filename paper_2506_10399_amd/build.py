@@ -11,7 +11,7 @@ SRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libficgcn.so")
 BUILD = os.path.join(os.path.dirname(HERE), "_build")
 SOURCES = ["context.cpp", "encode.cpp", "capi.cpp", "plan.cpp", "gcn.cpp",
-           "ntt.hip", "ops.hip", "sample.hip", "gcn_kernels.hip",
+           "ntt.hip", "ntt_fused.hip", "ops.hip", "sample.hip", "gcn_kernels.hip",
            "ks_batch.hip", "gcn_mfma.hip", "search.cpp", "mlp.hip", "server.cpp", "radix2.cpp", "encode_gpu.hip",
            "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

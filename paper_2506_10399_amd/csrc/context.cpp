@@ -4,6 +4,7 @@
 // below 2^q_bits with q = 1 (mod 2N), in descending order, then the alpha
 // largest primes below 2^p_bits with p = 1 (mod 2N) as the special modulus P
 // of hybrid key switching.
+#include <algorithm>
 #include <stdexcept>
 #include <thread>
 
@@ -30,7 +31,7 @@ Mod make_mod(uint64_t q) {
   // floor(2^128 / q) = floor((2^128 - 1) / q) for q not a power of two
   u128 all = ~(u128)0;
   u128 r = all / q;
-  return Mod{q, (uint64_t)(r >> 64), (uint64_t)r};
+  return Mod{q, (uint64_t)(r >> 64), (uint64_t)r, 1.0 / (double)q};
 }
 
 static bool miller_rabin(uint64_t n) {
@@ -134,6 +135,153 @@ void build_context(ckks_ctx* c) {
   c->h_mods.swap(mods);
 }
 
+// ModDown and rescale constants of every level.  h = floor(P / 2) = (P - 1) / 2 (P odd), so its
+// residue modulo m is (P mod m - 1) 2^-1 mod m.
+static void level_constants(ckks_ctx* c) {
+  auto p_mod = [&](uint64_t m) {
+    uint64_t v = 1;
+    for (int u = 0; u < c->alpha; ++u) v = (uint64_t)((u128)v * (c->mod[c->L + u] % m) % m);
+    return v;
+  };
+  MDK all{};
+  for (int t = 0; t < c->alpha; ++t) {
+    const uint64_t pm = c->mod[c->L + t];
+    all.hP[t] = (uint64_t)((u128)sub_mod(p_mod(pm), 1, pm) * invmod(2, pm) % pm);
+  }
+  c->mdk.assign(c->L, MDK{});
+  c->rsk.assign(c->L, RSK{});
+  for (int level = 0; level < c->L; ++level) {
+    const uint64_t q = c->mod[level], P = p_mod(q);
+    all.hQ[level] = (uint64_t)((u128)sub_mod(P, 1, q) * invmod(2, q) % q);
+    all.pinv[level] = invmod(P, q);
+    all.pinv_s[level] = shoup(all.pinv[level], q);
+    c->mdk[level] = all;
+    RSK& r = c->rsk[level];
+    for (int i = 0; i < level; ++i) {
+      const uint64_t qi = c->mod[i];
+      r.h[i] = (q / 2) % qi;
+      r.inv[i] = invmod(q % qi, qi);
+      r.inv_s[i] = shoup(r.inv[i], qi);
+    }
+  }
+}
+
+// The maps of the transforms fused with base conversions (ntt_fused.hip), for every level:
+// one table of source and destination entries for ModUp's digits, ModDown and the two rescales.
+static void mid_tables(ckks_ctx* c) {
+  std::vector<MidSrc> src;
+  std::vector<MidDst> dst;
+  auto source = [&](int mi, uint64_t scale, uint64_t shift) {
+    const uint64_t q = c->mod[mi];
+    MidSrc s{};
+    s.q = q;
+    s.qinv = 1.0 / (double)q;
+    s.c = scale;
+    s.cs = shoup(scale, q);
+    s.sh = shift;
+    s.mi = mi;
+    return s;
+  };
+  auto dest = [&](int mi, int pos) {
+    MidDst d{};
+    d.q = c->mod[mi];
+    d.qinv = 1.0 / (double)d.q;
+    d.mi = mi;
+    d.pos = pos;
+    return d;
+  };
+  // product of the other sources' primes modulo m
+  auto hat = [&](const std::vector<int>& srcs, int t, uint64_t m) {
+    uint64_t v = 1;
+    for (int u = 0; u < (int)srcs.size(); ++u)
+      if (u != t) v = (uint64_t)((u128)v * (c->mod[srcs[u]] % m) % m);
+    return v;
+  };
+  auto mul = [](uint64_t a, uint64_t b, uint64_t q) { return (uint64_t)((u128)a * b % q); };
+  // fast base conversion of `srcs` (at most two) to the listed destinations; half: ModDown's rounding
+  auto bconv = [&](const std::vector<int>& srcs, const std::vector<std::pair<int, int>>& dsts, const MDK* half) {
+    for (int t = 0; t < 2; ++t) {
+      if (t >= (int)srcs.size()) {
+        src.push_back(MidSrc{});
+        continue;
+      }
+      const uint64_t q = c->mod[srcs[t]], inv = invmod(hat(srcs, t, q), q);
+      src.push_back(source(srcs[t], mul(inv, c->h_ninv[srcs[t]], q), half ? mul(half->hP[t], inv, q) : 0));
+    }
+    for (const auto& d : dsts) {
+      MidDst e = dest(d.first, d.second);
+      for (int t = 0; t < (int)srcs.size(); ++t) {
+        e.a[t] = hat(srcs, t, e.q);
+        e.a[2 + t] = shoup(e.a[t], e.q);
+      }
+      e.a[4] = half ? half->hQ[d.second] : 0;
+      dst.push_back(e);
+    }
+  };
+  const int a = c->alpha;
+  c->mid.assign(c->L, MidLevel{});
+  for (int level = 0; level < c->L; ++level) {
+    MidLevel& m = c->mid[level];
+    const int l1 = level + 1, ext = l1 + a;
+    if (a <= 2) {
+      m.up_s = src.size();
+      m.up_d = dst.size();
+      for (int d = 0; d * a < l1; ++d) {
+        const int lo = d * a, hi = std::min(lo + a, l1);
+        std::vector<int> s;
+        std::vector<std::pair<int, int>> to;
+        for (int i = lo; i < hi; ++i) s.push_back(i);
+        for (int i = 0; i < l1; ++i)
+          if (i < lo || i >= hi) to.push_back({i, i});
+        for (int k = 0; k < a; ++k) to.push_back({c->L + k, l1 + k});
+        bconv(s, to, nullptr);
+        while ((int)(dst.size() - m.up_d) < (d + 1) * ext) dst.push_back(MidDst{});   // ext entries a digit
+      }
+      m.down_s = src.size();
+      m.down_d = dst.size();
+      std::vector<int> s;
+      std::vector<std::pair<int, int>> to;
+      for (int k = 0; k < a; ++k) s.push_back(c->L + k);
+      for (int i = 0; i < l1; ++i) to.push_back({i, i});
+      bconv(s, to, &c->mdk[level]);
+    }
+    if (level >= 1) {
+      const RSK& r = c->rsk[level];
+      const uint64_t ql = c->mod[level];
+      m.rs_s = src.size();
+      m.rs_d = dst.size();
+      src.push_back(source(level, c->h_ninv[level], ql / 2));
+      for (int i = 0; i < level; ++i) {
+        MidDst e = dest(i, i);
+        e.a[0] = r.h[i];
+        dst.push_back(e);
+      }
+    }
+    if (level >= 2) {
+      const RSK &r1 = c->rsk[level], &r2 = c->rsk[level - 1];
+      m.rs2_s = src.size();
+      m.rs2_d = dst.size();
+      // limb l-1 gets its half after the first correction (e), limb l its own at once
+      MidSrc lower = source(level - 1, c->h_ninv[level - 1], 0);
+      lower.e[0] = r1.h[level - 1];
+      lower.e[1] = r1.inv[level - 1];
+      lower.e[2] = r1.inv_s[level - 1];
+      src.push_back(lower);
+      src.push_back(source(level, c->h_ninv[level], c->mod[level] / 2));
+      for (int i = 0; i < level - 1; ++i) {
+        MidDst e = dest(i, i);
+        const uint64_t v[6] = {r1.h[i], r2.h[i], r1.inv[i], r1.inv_s[i], r2.inv[i], r2.inv_s[i]};
+        std::copy(v, v + 6, e.a);
+        dst.push_back(e);
+      }
+    }
+  }
+  HIPCHECK(hipMalloc(&c->mid_src, std::max<size_t>(1, src.size()) * sizeof(MidSrc)));
+  HIPCHECK(hipMemcpy(c->mid_src, src.data(), src.size() * sizeof(MidSrc), hipMemcpyHostToDevice));
+  HIPCHECK(hipMalloc(&c->mid_dst, std::max<size_t>(1, dst.size()) * sizeof(MidDst)));
+  HIPCHECK(hipMemcpy(c->mid_dst, dst.data(), dst.size() * sizeof(MidDst), hipMemcpyHostToDevice));
+}
+
 void ensure_device(ckks_ctx* c) {
   if (c->on_device) return;
   HIPCHECK(hipGetDevice(&c->device));
@@ -157,12 +305,14 @@ void ensure_device(ckks_ctx* c) {
   up(&c->t.ninv_s, c->h_ninv_s);
   HIPCHECK(hipMalloc(&c->t.mods, c->h_mods.size() * sizeof(Mod)));
   HIPCHECK(hipMemcpy(c->t.mods, c->h_mods.data(), c->h_mods.size() * sizeof(Mod), hipMemcpyHostToDevice));
-  c->on_device = true;
   // every base-conversion table of the chain, so later calls find them built
   for (int level = 0; level < c->L; ++level) {
     for (int d = 0; d * c->alpha <= level; ++d) get_modup(c, level, d);
     get_moddown(c, level);
   }
+  level_constants(c);
+  mid_tables(c);
+  c->on_device = true;
 }
 
 // FastBConv constants: hat_b = prod_{s' != s} b_{s'}; hat_inv[s] = hat_b^-1 mod b_s;
@@ -301,6 +451,8 @@ ckks_ctx::~ckks_ctx() {
   if (enc_pos) (void)hipFree(enc_pos);
   if (enc_flag) (void)hipFree(enc_flag);
   if (t.mods) (void)hipFree(t.mods);
+  if (mid_src) (void)hipFree(mid_src);
+  if (mid_dst) (void)hipFree(mid_dst);
   for (auto& kv : modup) { (void)hipFree(kv.second.dev); (void)hipFree(kv.second.idx); }
   for (auto& kv : moddown) { (void)hipFree(kv.second.dev); (void)hipFree(kv.second.idx); }
 }

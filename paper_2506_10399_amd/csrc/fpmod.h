@@ -24,11 +24,8 @@ namespace ficgcn {
 //   * a sum or difference t in (-2q, 2q) is brought back by t - q*rint(t/q),
 //     which lands in [-q/2 - 1, q/2 + 1] (t/q is known to 2^-51);
 // three fp64 operations each, in place of a compare, an add and two selects.
-// Sums are brought back on every other stage only (and on a pass's last stage):
-// a product with a in (-2q, 2q) still lands in (-3q/2, 3q/2) (the estimate
-// error grows to below 1/2 + 1/2, |lo| < q/2), so the next stage's sums stay
-// within (-4q, 4q), exact integers below 2^52, and t - q*rint(t/q) brings them
-// back as before.  The last pass maps the values to [0, q) once.
+// A transform brings its sums back on some stages only (ntt_dev.h has the bounds); the
+// last pass maps the values to [0, q) once.
 __device__ __forceinline__ uint64_t f2b(double d) { return (uint64_t)__double_as_longlong(d); }
 __device__ __forceinline__ double b2f(uint64_t b) { return __longlong_as_double((long long)b); }
 // Exact conversions for integers below 2^52: the double 2^52 + v has v as its

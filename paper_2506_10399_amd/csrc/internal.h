@@ -65,6 +65,45 @@ struct BConv {
 }  // namespace ficgcn
 
 namespace ficgcn {
+// ModDown constants of a level: h = floor(P / 2) modulo the special primes and the Q primes,
+// P^-1 mod q_i with its Shoup companion
+struct MDK {
+  uint64_t hP[8];
+  uint64_t hQ[64];
+  uint64_t pinv[64], pinv_s[64];
+};
+// Rescale constants of a level: floor(q_l / 2) mod q_i, q_l^-1 mod q_i with its Shoup companion
+struct RSK {
+  uint64_t h[64];
+  uint64_t inv[64], inv_s[64];
+};
+
+// Entries of the fused conversions' tables (ntt_fused.hip).  A source limb's coefficient x (not yet
+// divided by N) becomes y = x c + sh modulo its prime, with the division by N in c; what a[] and e[]
+// hold is the map's own (mid_tables).
+struct MidSrc {
+  uint64_t q;
+  double qinv;
+  uint64_t c, cs, sh;
+  uint64_t e[3];
+  int32_t mi, pad;
+};
+struct MidDst {
+  uint64_t q;
+  double qinv;
+  uint64_t a[6];
+  int32_t mi, pos;   // modulus index; limb of the output
+};
+// first entries of one level's maps
+struct MidLevel {
+  size_t up_s, up_d;       // ModUp: per digit two sources and level+1+alpha destinations
+  size_t down_s, down_d;   // ModDown
+  size_t rs_s, rs_d;       // rescale
+  size_t rs2_s, rs2_d;     // two rescales in a row
+};
+}  // namespace ficgcn
+
+namespace ficgcn {
 // Device buffers of one recorded launch sequence (a layer captured in a HIP
 // graph).  RECORD: every table upload and scratch request gets a buffer of
 // its own, kept in call order; REPLAY: the same calls get the same buffers
@@ -93,6 +132,11 @@ struct ckks_ctx {
   int device = 0;
   std::map<std::pair<int, int>, ficgcn::BConv> modup;   // (level, digit)
   std::map<int, ficgcn::BConv> moddown;                  // level
+  std::vector<ficgcn::MDK> mdk;                          // per level, built with the device tables
+  std::vector<ficgcn::RSK> rsk;
+  std::vector<ficgcn::MidLevel> mid;
+  ficgcn::MidSrc* mid_src = nullptr;
+  ficgcn::MidDst* mid_dst = nullptr;
   // grow-only scratch buffers by slot: ops.hip 1-9, sample/capi 10-29, gcn.cpp 30-49 and 70-79,
   // ks_batch.hip 50-64 and 80-89, search.cpp 65-66 (a slot's memory moves when it grows, so one
   // user per slot)
@@ -168,6 +212,12 @@ uint64_t galois_elt(ckks_ctx* c, int64_t step);
 void ntt_fwd(ckks_ctx* c, uint64_t* base, int n_limbs, LimbMap map, int n_polys, size_t poly_stride,
              int skip_alpha = 0, int skip_q = 0);
 void ntt_inv(ckks_ctx* c, uint64_t* base, int n_limbs, LimbMap map, int n_polys, size_t poly_stride);
+// One pass alone, at the split ntt_mid_log gives (log2 of the column pass's points, at most 8): the
+// forward transform's row pass, the inverse transform's row pass (its other half is a fused kernel).
+int ntt_mid_log(const ckks_ctx* c);
+void ntt_fwd_rows(ckks_ctx* c, uint64_t* base, int n_limbs, LimbMap map, int n_polys, size_t poly_stride,
+                  int skip_alpha = 0, int skip_q = 0);
+void ntt_inv_rows(ckks_ctx* c, uint64_t* base, int n_limbs, LimbMap map, int n_polys, size_t poly_stride);
 
 // ---- elementwise and key-switching kernels (ops.hip) ----
 struct PtrList {

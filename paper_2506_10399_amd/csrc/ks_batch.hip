@@ -18,9 +18,10 @@
 #include <algorithm>
 #include <numeric>
 
-#include "internal.h"
 #include "fpmod.h"
 #include "ks_batch.h"
+#include "ks_common.h"
+#include "ntt_fused.h"
 
 namespace ficgcn {
 
@@ -28,23 +29,7 @@ void zero_fill(ckks_ctx* c, uint64_t* p, size_t words);
 
 constexpr int KB = 256;
 
-// Accesses through pointers read from device tables (job lists, term lists,
-// pointer arrays).  The compiler cannot tell that such a pointer addresses
-// global memory and would emit flat accesses, which also count on the
-// scalar-load counter: every read of the next table entry would then wait for
-// all vector loads in flight.  These pin the access to the global segment.
-typedef __attribute__((address_space(1))) uint64_t gu64;
-__device__ __forceinline__ uint64_t gld(const uint64_t* p) { return *(const gu64*)p; }
-__device__ __forceinline__ void gst(uint64_t* p, uint64_t v) { *(gu64*)p = v; }
 __device__ const uint64_t k_one_word = 1;
-
-__device__ __forceinline__ uint32_t auto_idx(uint32_t k, uint64_t g, int log_n) {
-  // evaluation index k holds A(psi^(2 brev(k) + 1)); sigma_g reads the index of psi^(g (2 brev(k) + 1))
-  uint32_t N2 = 2u << log_n;
-  uint32_t e = 2u * bitrev(k, log_n) + 1u;
-  uint32_t ge = (uint32_t)(((uint64_t)e * g) & (N2 - 1));
-  return bitrev((ge - 1u) >> 1, log_n);
-}
 
 // tmp[u] = sources[u] (l1 limbs)
 __global__ void k_gather(uint64_t* __restrict__ tmp, const uint64_t* const* __restrict__ src, int l1, int log_n) {
@@ -161,12 +146,6 @@ static std::vector<int> key_runs(const std::vector<KSJob>& jobs) {
   return start;
 }
 
-struct MDK {
-  uint64_t hP[8];                 // floor(P/2) mod p_t
-  uint64_t hQ[64];                // floor(P/2) mod q_i
-  uint64_t pinv[64], pinv_s[64];  // P^-1 mod q_i, Shoup
-};
-
 // conv[z][i] = FastBConv_{P -> q_i}([acc_P + floor(P/2)]) - floor(P/2)   (coefficient form)
 __global__ void k_moddown_conv_batch(const uint64_t* __restrict__ acc, int ext, int l1, const int* __restrict__ src_mod,
                                      const int* __restrict__ dst_mod, int ns, const uint64_t* __restrict__ table,
@@ -232,31 +211,55 @@ __global__ void k_ks_final(const uint64_t* __restrict__ acc, const uint64_t* __r
   gst(gd.out + o, add_mod(a, reduce128(s, md), q));
 }
 
-static MDK mdk(ckks_ctx* c, int level) {
-  MDK k{};
-  for (int t = 0; t < c->alpha; ++t) {
-    const uint64_t pm = c->mod[c->L + t];
-    uint64_t P_mod = 1;
-    for (int u = 0; u < c->alpha; ++u) P_mod = (uint64_t)((u128)P_mod * (c->mod[c->L + u] % pm) % pm);
-    k.hP[t] = (uint64_t)((u128)sub_mod(P_mod, 1, pm) * invmod(2, pm) % pm);
-  }
-  for (int i = 0; i <= level; ++i) {
-    const uint64_t q = c->mod[i];
-    uint64_t P_mod = 1;
-    for (int u = 0; u < c->alpha; ++u) P_mod = (uint64_t)((u128)P_mod * (c->mod[c->L + u] % q) % q);
-    k.hQ[i] = (uint64_t)((u128)sub_mod(P_mod, 1, q) * invmod(2, q) % q);
-    k.pinv[i] = invmod(P_mod, q);
-    k.pinv_s[i] = shoup(k.pinv[i], q);
-  }
-  return k;
-}
-
 enum { S_KB_TMP = 50, S_KB_D, S_KB_ACC, S_KB_CONV, S_KB_JOBS, S_KB_SRC, S_KB_GRP, S_TB_JOBS, S_RS_PTR, S_RS_LAST,
        S_RS_D, S_GM_TERMS, S_GM_START, S_GM_OUT, S_KB_RUNS };
 
 template <typename T>
 static T* upload(ckks_ctx* c, int slot, const std::vector<T>& v) {
   return (T*)dev_table(c, slot, v.data(), v.size() * sizeof(T));
+}
+
+// ModUp of a batch's sources (device table of U polynomials [l1][N]) into D [U][nd][ext][N]
+static void modup_batch(ckks_ctx* c, int level, const uint64_t* const* sd, int U, uint64_t* tmp, uint64_t* D) {
+  if (fused_basis(c)) {
+    modup_polys(c, level, sd, nullptr, U, tmp, D);
+    return;
+  }
+  const size_t N = c->N;
+  const int l1 = level + 1, ext = l1 + c->alpha;
+  const int nd = (l1 + c->alpha - 1) / c->alpha;
+  DigitTables dt{};
+  for (int d = 0; d < nd; ++d) {
+    const BConv& bc = get_modup(c, level, d);
+    dt.tab[d] = bc.dev;
+    dt.idx[d] = bc.idx;
+    dt.n_src[d] = bc.n_src;
+    dt.n_dst[d] = bc.n_dst;
+  }
+  hipLaunchKernelGGL(k_gather, dim3(N / KB, l1, U), dim3(KB), 0, c->stream, tmp, sd, l1, c->log_n);
+  HIPCHECK(hipGetLastError());
+  ntt_inv(c, tmp, l1, lm_q(l1), U, (size_t)l1 * N);
+  hipLaunchKernelGGL(k_modup_conv, dim3(N / KB, nd, U), dim3(KB), 0, c->stream, tmp, sd, D, dt, c->alpha, l1, ext, nd,
+                     c->L, c->log_n, c->t.mods);
+  HIPCHECK(hipGetLastError());
+  // every extended limb to evaluation form except each digit's own limbs
+  ntt_fwd(c, D, ext, lm_ext(level, c->L), U * nd, (size_t)ext * N, c->alpha, l1);
+}
+
+// ModDown's conversion of Z accumulators [ext][N]: conv [Z][l1][N] in evaluation form
+static void moddown_conv_batch(ckks_ctx* c, int level, uint64_t* acc, int Z, const MDK& k, uint64_t* conv) {
+  if (fused_basis(c)) {
+    moddown_polys(c, level, acc, Z, conv, true);
+    return;
+  }
+  const size_t N = c->N;
+  const int l1 = level + 1, ext = l1 + c->alpha;
+  const BConv& md = get_moddown(c, level);
+  ntt_inv(c, acc + (size_t)l1 * N, c->alpha, LimbMap{c->L, 1 << 30, 0}, Z, (size_t)ext * N);
+  hipLaunchKernelGGL(k_moddown_conv_batch, dim3(N / KB, Z), dim3(KB), 0, c->stream, acc, ext, l1, md.idx,
+                     md.idx + md.n_src, md.n_src, (const uint64_t*)md.dev, k, conv, c->log_n, c->t.mods);
+  HIPCHECK(hipGetLastError());
+  ntt_fwd(c, conv, l1, lm_q(l1), Z, (size_t)l1 * N);
 }
 
 // scratch bound of one chunk of a key-switch batch
@@ -279,16 +282,7 @@ void keyswitch_batch(ckks_ctx* c, int level, const std::vector<const uint64_t*>&
   const size_t per_job = (size_t)2 * (ext + l1) * N * 8;
   const size_t per_src = (size_t)(nd * ext + l1) * N * 8;
   std::vector<char> touched(n_grp, 0);
-  const MDK k = mdk(c, level);
-  DigitTables dt{};
-  for (int d = 0; d < nd; ++d) {
-    const BConv& bc = get_modup(c, level, d);
-    dt.tab[d] = bc.dev;
-    dt.idx[d] = bc.idx;
-    dt.n_src[d] = bc.n_src;
-    dt.n_dst[d] = bc.n_dst;
-  }
-  const BConv& md = get_moddown(c, level);
+  const MDK& k = c->mdk[level];
   size_t a = 0;
   while (a < jobs.size()) {
     // chunk [a, b): sources remapped to a dense local list
@@ -324,21 +318,22 @@ void keyswitch_batch(ckks_ctx* c, int level, const std::vector<const uint64_t*>&
     const int U = (int)srcs.size(), R = (int)cj.size();
     KSJob* jd = upload(c, S_KB_JOBS, cj);
     const uint64_t* const* sd = upload(c, S_KB_SRC, srcs);
-    GroupDesc* gd = upload(c, S_KB_GRP, gds);
+    // one unmasked switch per output: the last step is part of the transform before it
+    std::vector<FinalJob> finals;
+    bool single = fused_basis(c) && gds.size() == cj.size();
+    for (const KSJob& jb : cj) single = single && !jb.pt;
+    if (single)
+      for (int r = 0; r < R; ++r)
+        finals.push_back(FinalJob{gds[r].out, cj[r].add0, cj[r].add1, cj[r].g, gds[r].accumulate, 0});
+    GroupDesc* gd = single ? nullptr : upload(c, S_KB_GRP, gds);
+    FinalJob* fd = single ? upload(c, S_KB_GRP, finals) : nullptr;
     uint64_t* tmp = (uint64_t*)dev_scratch(c, S_KB_TMP, (size_t)U * l1 * N * 8);
     uint64_t* D = (uint64_t*)dev_scratch(c, S_KB_D, (size_t)U * nd * ext * N * 8);
     uint64_t* acc = (uint64_t*)dev_scratch(c, S_KB_ACC, (size_t)R * 2 * ext * N * 8);
     uint64_t* conv = (uint64_t*)dev_scratch(c, S_KB_CONV, (size_t)R * 2 * l1 * N * 8);
     {
       ProfScope pm(c, "modup");
-      hipLaunchKernelGGL(k_gather, dim3(N / KB, l1, U), dim3(KB), 0, c->stream, tmp, sd, l1, c->log_n);
-      HIPCHECK(hipGetLastError());
-      ntt_inv(c, tmp, l1, lm_q(l1), U, (size_t)l1 * N);
-      hipLaunchKernelGGL(k_modup_conv, dim3(N / KB, nd, U), dim3(KB), 0, c->stream, tmp, sd, D, dt, c->alpha, l1, ext,
-                         nd, c->L, c->log_n, c->t.mods);
-      HIPCHECK(hipGetLastError());
-      // every extended limb to evaluation form except each digit's own limbs
-      ntt_fwd(c, D, ext, lm_ext(level, c->L), U * nd, (size_t)ext * N, c->alpha, l1);
+      modup_batch(c, level, sd, U, tmp, D);
     }
     {
       ProfScope pk(c, "keymac");
@@ -369,14 +364,15 @@ void keyswitch_batch(ckks_ctx* c, int level, const std::vector<const uint64_t*>&
     }
     {
       ProfScope pd(c, "moddown");
-      ntt_inv(c, acc + (size_t)l1 * N, c->alpha, LimbMap{c->L, 1 << 30, 0}, 2 * R, (size_t)ext * N);
-      hipLaunchKernelGGL(k_moddown_conv_batch, dim3(N / KB, 2 * R), dim3(KB), 0, c->stream, acc, ext, l1, md.idx,
-                         md.idx + md.n_src, md.n_src, (const uint64_t*)md.dev, k, conv, c->log_n, c->t.mods);
-      HIPCHECK(hipGetLastError());
-      ntt_fwd(c, conv, l1, lm_q(l1), 2 * R, (size_t)l1 * N);
-      hipLaunchKernelGGL(k_ks_final, dim3(N / KB, l1, 2 * gds.size()), dim3(KB), 0, c->stream, acc, conv, ext, l1, k,
-                         jd, gd, c->log_n, c->t.mods);
-      HIPCHECK(hipGetLastError());
+      if (finals.empty()) {
+        moddown_conv_batch(c, level, acc, 2 * R, k, conv);
+        hipLaunchKernelGGL(k_ks_final, dim3(N / KB, l1, 2 * gds.size()), dim3(KB), 0, c->stream, acc, conv, ext, l1,
+                           k, jd, gd, c->log_n, c->t.mods);
+        HIPCHECK(hipGetLastError());
+      } else {
+        moddown_polys(c, level, acc, 2 * R, conv, false);
+        moddown_final(c, level, acc, conv, fd, FinalJob{}, R);
+      }
     }
     // the host lists of this chunk are released below and the device lists reused
     stream_sync(c);
@@ -478,7 +474,7 @@ __global__ void k_keymac_masked_runs(const uint64_t* __restrict__ D, const KSJob
   const Mod md = mods[m];
   const int ra = (int)((int64_t)n_runs * seg / n_seg), rb = (int)((int64_t)n_runs * (seg + 1) / n_seg);
   if (fq && i < l1) {
-    const double qd = (double)md.q, qinv = 1.0 / qd;
+    const double qd = (double)md.q, qinv = md.qinv;
     auto cv = [](uint64_t v) { return b2f(to_fbits(v)); };
     double T0[NG], T1[NG];
     int cnt[NG];
@@ -679,14 +675,6 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
   zero_fill(c, A, (size_t)n_grp * 2 * ext * N);
   const size_t per_job = 0;   // a job's products go straight into its output's accumulator
   const size_t per_src = (size_t)(nd * ext + l1) * N * 8;
-  DigitTables dt{};
-  for (int d = 0; d < nd; ++d) {
-    const BConv& bc = get_modup(c, level, d);
-    dt.tab[d] = bc.dev;
-    dt.idx[d] = bc.idx;
-    dt.n_src[d] = bc.n_src;
-    dt.n_dst[d] = bc.n_dst;
-  }
   size_t a = 0;
   while (a < jl.size()) {
     std::vector<int> local(sources.size(), -1);
@@ -730,13 +718,7 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
     uint64_t* D = (uint64_t*)dev_scratch(c, S_KB_D, (size_t)U * nd * ext * N * 8);
     {
       ProfScope pm(c, "modup");
-      hipLaunchKernelGGL(k_gather, dim3(N / KB, l1, U), dim3(KB), 0, c->stream, tmp, sd, l1, c->log_n);
-      HIPCHECK(hipGetLastError());
-      ntt_inv(c, tmp, l1, lm_q(l1), U, (size_t)l1 * N);
-      hipLaunchKernelGGL(k_modup_conv, dim3(N / KB, nd, U), dim3(KB), 0, c->stream, tmp, sd, D, dt, c->alpha, l1, ext,
-                         nd, c->L, c->log_n, c->t.mods);
-      HIPCHECK(hipGetLastError());
-      ntt_fwd(c, D, ext, lm_ext(level, c->L), U * nd, (size_t)ext * N, c->alpha, l1);
+      modup_batch(c, level, sd, U, tmp, D);
     }
     {
       ProfScope pk(c, "keymac");
@@ -795,8 +777,7 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
   // forward NTT, then out (+)= (A_Q - conv) P^-1 + sum sigma(add0) (.) pt
   {
     ProfScope pd(c, "moddown");
-    const MDK k = mdk(c, level);
-    const BConv& md = get_moddown(c, level);
+    const MDK& k = c->mdk[level];
     std::vector<MaskGroup> mg(n_grp, MaskGroup{0, 0});
     for (size_t r = 0; r < jobs.size(); ++r) {
       const int g = jobs[r].grp;
@@ -807,11 +788,7 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
     MaskGroup* mgd = upload(c, S_KM_GRP, mg);
     uint64_t* const* od = upload(c, S_KM_OUT, outs);
     uint64_t* conv = (uint64_t*)dev_scratch(c, S_KM_CONV, (size_t)n_grp * 2 * l1 * N * 8);
-    ntt_inv(c, A + (size_t)l1 * N, c->alpha, LimbMap{c->L, 1 << 30, 0}, 2 * n_grp, (size_t)ext * N);
-    hipLaunchKernelGGL(k_moddown_conv_batch, dim3(N / KB, 2 * n_grp), dim3(KB), 0, c->stream, A, ext, l1, md.idx,
-                       md.idx + md.n_src, md.n_src, (const uint64_t*)md.dev, k, conv, c->log_n, c->t.mods);
-    HIPCHECK(hipGetLastError());
-    ntt_fwd(c, conv, l1, lm_q(l1), 2 * n_grp, (size_t)l1 * N);
+    moddown_conv_batch(c, level, A, 2 * n_grp, k, conv);
     hipLaunchKernelGGL(k_masked_final, dim3(N / KB, l1, 2 * n_grp), dim3(KB), 0, c->stream, A, conv, ext, l1, k, jall,
                        mgd, od, accumulate ? 1 : 0, c->log_n, c->t.mods);
     HIPCHECK(hipGetLastError());
@@ -844,29 +821,6 @@ void tensor_batch(ckks_ctx* c, int level, const std::vector<TensorJob>& jobs) {
   stream_sync(c);
 }
 
-struct RSK {
-  uint64_t h[64];               // floor(q_l / 2) mod q_i
-  uint64_t inv[64], inv_s[64];  // q_l^-1 mod q_i, Shoup
-};
-
-__global__ void k_rs_gather(uint64_t* __restrict__ last, uint64_t* const* __restrict__ cts, int lvl, int log_n) {
-  const size_t N = (size_t)1 << log_n;
-  const size_t j = blockIdx.x * (size_t)KB + threadIdx.x;
-  const int z = blockIdx.y;   // ct * 2 + component
-  last[(size_t)z * N + j] = gld(cts[z >> 1] + ((size_t)(z & 1) * (lvl + 1) + lvl) * N + j);
-}
-
-// d[z][i] = (h - ((x + h) mod q_l)) mod q_i for the last limb x in coefficient form
-__global__ void k_rs_prep(const uint64_t* __restrict__ last, uint64_t* __restrict__ d, int lvl, uint64_t hl, RSK k,
-                          int log_n, const Mod* __restrict__ mods) {
-  const size_t N = (size_t)1 << log_n;
-  const size_t j = blockIdx.x * (size_t)KB + threadIdx.x;
-  const int i = blockIdx.y, z = blockIdx.z;
-  const uint64_t ql = mods[lvl].q, q = mods[i].q;
-  const uint64_t y = add_mod(last[(size_t)z * N + j], hl, ql);   // < q_l < q_i (descending chain)
-  d[((size_t)z * lvl + i) * N + j] = sub_mod(k.h[i], y, q);
-}
-
 // c'_i = (c_i + d_i) q_l^-1, compacted in place from [2][l+1][N] to [2][l][N].
 // One thread walks the limbs of one component upwards, so a limb is read
 // before the write of the next-lower position reaches it; the two
@@ -895,21 +849,8 @@ void rescale_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
   uint64_t* const* cd = upload(c, S_RS_PTR, cts);
   uint64_t* last = (uint64_t*)dev_scratch(c, S_RS_LAST, (size_t)2 * n * N * 8);
   uint64_t* d = (uint64_t*)dev_scratch(c, S_RS_D, (size_t)2 * n * level * N * 8);
-  hipLaunchKernelGGL(k_rs_gather, dim3(N / KB, 2 * n), dim3(KB), 0, c->stream, last, cd, level, c->log_n);
-  HIPCHECK(hipGetLastError());
-  ntt_inv(c, last, 1, LimbMap{level, 1 << 30, 0}, 2 * n, N);
-  RSK k{};
-  const uint64_t ql = c->mod[level], hl = ql / 2;
-  for (int i = 0; i < level; ++i) {
-    const uint64_t q = c->mod[i];
-    k.h[i] = hl % q;
-    k.inv[i] = invmod(ql % q, q);
-    k.inv_s[i] = shoup(k.inv[i], q);
-  }
-  hipLaunchKernelGGL(k_rs_prep, dim3(N / KB, level, 2 * n), dim3(KB), 0, c->stream, last, d, level, hl, k, c->log_n,
-                     c->t.mods);
-  HIPCHECK(hipGetLastError());
-  ntt_fwd(c, d, level, lm_q(level), 2 * n, (size_t)level * N);
+  const RSK& k = c->rsk[level];
+  rescale_prep(c, level, cd, nullptr, n, last, d);
   hipLaunchKernelGGL(k_rs_final, dim3(N / KB, 2 * n), dim3(KB), 0, c->stream, cd, d, level, k, c->log_n, c->t.mods);
   HIPCHECK(hipGetLastError());
   stream_sync(c);
@@ -926,36 +867,11 @@ void rescale_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
 // limbs instead of l + (l - 1).  h_k = floor(q_k / 2).
 constexpr int RS2_MAX = 32;
 struct RSK2 {
-  uint64_t h1[RS2_MAX], h2[RS2_MAX];            // h_l, h_{l-1} mod q_i
+  uint64_t h1[RS2_MAX], h2[RS2_MAX];            // floor(q_l / 2), floor(q_{l-1} / 2) mod q_i
   uint64_t inv1[RS2_MAX], inv1_s[RS2_MAX];      // q_l^-1 mod q_i, Shoup
   uint64_t inv2[RS2_MAX], inv2_s[RS2_MAX];      // q_{l-1}^-1 mod q_i
   uint64_t inv12[RS2_MAX], inv12_s[RS2_MAX];    // (q_l q_{l-1})^-1 mod q_i
 };
-
-// last[z][0] = limb l-1, last[z][1] = limb l of component z
-__global__ void k_rs2_gather(uint64_t* __restrict__ last, uint64_t* const* __restrict__ cts, int lvl, int log_n) {
-  const size_t N = (size_t)1 << log_n;
-  const size_t j = blockIdx.x * (size_t)KB + threadIdx.x;
-  const int z = blockIdx.y, u = blockIdx.z;   // z = ct * 2 + component; u = 0: limb l-1, 1: limb l
-  last[((size_t)z * 2 + u) * N + j] = gld(cts[z >> 1] + ((size_t)(z & 1) * (lvl + 1) + lvl - 1 + u) * N + j);
-}
-
-// f[z][i] = (d_i q_l^-1 + e_i) q_{l-1}^-1 mod q_i for i < l - 1, coefficient form
-__global__ void k_rs2_prep(const uint64_t* __restrict__ last, uint64_t* __restrict__ f, int lvl, RSK2 k, int log_n,
-                           const Mod* __restrict__ mods) {
-  const size_t N = (size_t)1 << log_n;
-  const size_t j = blockIdx.x * (size_t)KB + threadIdx.x;
-  const int i = blockIdx.y, z = blockIdx.z;
-  const uint64_t ql = mods[lvl].q, qm = mods[lvl - 1].q, q = mods[i].q;
-  const uint64_t xm = last[((size_t)z * 2 + 0) * N + j], xl = last[((size_t)z * 2 + 1) * N + j];
-  const uint64_t y1 = add_mod(xl, ql / 2, ql);                        // < q_l < q_{l-1} < q_i (descending chain)
-  const uint64_t dm = sub_mod(k.h1[lvl - 1], y1, qm);
-  const uint64_t y = mul_shoup(add_mod(xm, dm, qm), k.inv1[lvl - 1], k.inv1_s[lvl - 1], qm);
-  const uint64_t y2 = add_mod(y, qm / 2, qm);                         // < q_{l-1} < q_i
-  const uint64_t d = sub_mod(k.h1[i], y1, q), e = sub_mod(k.h2[i], y2, q);
-  const uint64_t t = add_mod(mul_shoup(d, k.inv1[i], k.inv1_s[i], q), e, q);
-  f[((size_t)z * (lvl - 1) + i) * N + j] = mul_shoup(t, k.inv2[i], k.inv2_s[i], q);
-}
 
 // c''_i = c_i (q_l q_{l-1})^-1 + f_i, compacted in place from [2][l+1][N] to
 // [2][l-1][N]: one thread walks the limbs of one component upwards, so each
@@ -988,28 +904,22 @@ void rescale2_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
   uint64_t* const* cd = upload(c, S_RS_PTR, cts);
   uint64_t* last = (uint64_t*)dev_scratch(c, S_RS_LAST, (size_t)2 * n * 2 * N * 8);
   uint64_t* f = (uint64_t*)dev_scratch(c, S_RS_D, (size_t)2 * n * (level - 1) * N * 8);
-  hipLaunchKernelGGL(k_rs2_gather, dim3(N / KB, 2 * n, 2), dim3(KB), 0, c->stream, last, cd, level, c->log_n);
-  HIPCHECK(hipGetLastError());
-  ntt_inv(c, last, 2, LimbMap{level - 1, 1 << 30, 0}, 2 * n, 2 * N);
   RSK2 k{};
-  const uint64_t ql = c->mod[level], qm = c->mod[level - 1];
+  const RSK &r1 = c->rsk[level], &r2 = c->rsk[level - 1];
   for (int i = 0; i < level; ++i) {
     const uint64_t q = c->mod[i];
-    k.h1[i] = (ql / 2) % q;
-    k.inv1[i] = invmod(ql % q, q);
-    k.inv1_s[i] = shoup(k.inv1[i], q);
+    k.h1[i] = r1.h[i];
+    k.inv1[i] = r1.inv[i];
+    k.inv1_s[i] = r1.inv_s[i];
     if (i < level - 1) {
-      k.h2[i] = (qm / 2) % q;
-      k.inv2[i] = invmod(qm % q, q);
-      k.inv2_s[i] = shoup(k.inv2[i], q);
+      k.h2[i] = r2.h[i];
+      k.inv2[i] = r2.inv[i];
+      k.inv2_s[i] = r2.inv_s[i];
       k.inv12[i] = (uint64_t)((u128)k.inv1[i] * k.inv2[i] % q);
       k.inv12_s[i] = shoup(k.inv12[i], q);
     }
   }
-  hipLaunchKernelGGL(k_rs2_prep, dim3(N / KB, level - 1, 2 * n), dim3(KB), 0, c->stream, last, f, level, k, c->log_n,
-                     c->t.mods);
-  HIPCHECK(hipGetLastError());
-  ntt_fwd(c, f, level - 1, lm_q(level - 1), 2 * n, (size_t)(level - 1) * N);
+  rescale2_prep(c, level, cd, n, last, f);
   hipLaunchKernelGGL(k_rs2_final, dim3(N / KB, 2 * n), dim3(KB), 0, c->stream, cd, f, level, k, c->log_n, c->t.mods);
   HIPCHECK(hipGetLastError());
   stream_sync(c);
@@ -1161,7 +1071,7 @@ __global__ void __launch_bounds__(GM_TB) k_group_mac_np(const MacTermNP* __restr
     // fp64 residues (every prime in (2^49, 2^50)): each product a signed representative in
     // (-q, q), summed in a double; six terms at most between reductions keep every sum an
     // exact integer below 2^53
-    const double qd = (double)m.q, qinv = 1.0 / qd;
+    const double qd = (double)m.q, qinv = m.qinv;
     double S[NP][4];
 #pragma unroll
     for (int c = 0; c < NP; ++c)

@@ -43,6 +43,7 @@ FICGCN_FD uint64_t mul_shoup_lazy(uint64_t a, uint64_t w, uint64_t ws, uint64_t 
 struct Mod {
   uint64_t q;
   uint64_t r_hi, r_lo;   // floor(2^128 / q)
+  double qinv;           // 1 / q
 };
 
 // (hi * 2^64 + lo) mod q

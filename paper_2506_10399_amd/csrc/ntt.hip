@@ -21,11 +21,13 @@
 // global loads and stores coalesced).  Every twiddle a thread needs is read
 // before its stages run.  A workgroup handles COLS columns (column pass) or
 // chunks (row pass); COLS is picked per ring degree by the autotuner.
-// For the 50-bit Q primes (fp64 residue arithmetic below) the limb travels
+// The stages themselves are in ntt_dev.h.
+// For the 50-bit Q primes (fp64 residue arithmetic, fpmod.h) the limb travels
 // between the two passes as the bit patterns of its doubles: the first pass
 // converts on load, the second on store.
-#include "internal.h"
-#include "fpmod.h"
+#include <algorithm>
+
+#include "ntt_dev.h"
 
 namespace ficgcn {
 
@@ -35,260 +37,62 @@ __device__ __forceinline__ bool skip_limb(int limb, int poly, int skip_alpha, in
   return skip_alpha > 0 && limb < skip_q && limb / skip_alpha == poly % ((skip_q + skip_alpha - 1) / skip_alpha);
 }
 
-// Integer butterflies with lazy reduction (Harvey's, for q < 2^62): inside a forward
-// transform the values lie in [0, 4q), inside an inverse one in [0, 2q).  Shoup's
-// product without its correction lands in [0, 2q) for any 64-bit input, so
-//   forward CT: x <- x mod 2q (one conditional subtract), t = y w in [0, 2q),
-//               (x, y) <- (x + t, x - t + 2q), both in [0, 4q);
-//   inverse GS: (x, y) <- (x + y reduced to [0, 2q), (x - y + 2q) w in [0, 2q)).
-// The forward transform's last pass and the inverse's scaling by 1/N return [0, q).
-__device__ __forceinline__ void bf_fwd(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, uint64_t q) {
-  const uint64_t q2 = 2 * q;
-  const uint64_t a = x >= q2 ? x - q2 : x;
-  const uint64_t t = mul_shoup_lazy(y, w, ws, q);
-  x = a + t;
-  y = a - t + q2;
-}
-__device__ __forceinline__ void bf_inv(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, uint64_t q) {
-  const uint64_t q2 = 2 * q;
-  const uint64_t s = x + y;
-  const uint64_t d = x - y + q2;
-  x = s >= q2 ? s - q2 : s;
-  y = mul_shoup_lazy(d, w, ws, q);
-}
-// [0, 4q) -> [0, q)
-__device__ __forceinline__ uint64_t canon4(uint64_t x, uint64_t q) {
-  x = x >= 2 * q ? x - 2 * q : x;
-  return x >= q ? x - q : x;
-}
-
-
-template <bool FP>
-__device__ __forceinline__ void bfly_fwd(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, uint64_t q, double qd,
-                                         double qinv, bool red = true) {
-  if (FP) {
-    const double xd = b2f(x), v = fmulmod_s(b2f(y), b2f(w), qd, qinv);
-    x = f2b(red ? sred(xd + v, qd, qinv) : xd + v);
-    y = f2b(red ? sred(xd - v, qd, qinv) : xd - v);
-  } else {
-    bf_fwd(x, y, w, ws, q);
-  }
-}
-
-template <bool FP>
-__device__ __forceinline__ void bfly_inv(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, uint64_t q, double qd,
-                                         double qinv, bool red = true) {
-  if (FP) {
-    const double xd = b2f(x), yd = b2f(y);
-    x = f2b(red ? sred(xd + yd, qd, qinv) : xd + yd);
-    y = f2b(fmulmod_s(red ? sred(xd - yd, qd, qinv) : xd - yd, b2f(w), qd, qinv));
-  } else {
-    bf_inv(x, y, w, ws, q);
-  }
-}
-
 // One pass over one sub-transform set of a limb; FP selects the fp64 residue arithmetic.
 template <int LOGC, int COLS, bool INV, bool ROW, bool FP>
-__device__ __forceinline__ void ntt_pass_body(uint64_t* s, uint64_t* a, const uint64_t* __restrict__ W,
-                                              const uint64_t* __restrict__ Ws, const double* __restrict__ Wf,
-                                              uint64_t q, int N, int mi,
+__device__ __forceinline__ void ntt_pass_body(uint64_t* s, uint64_t* a, const Tw& t, int log_n, int mi,
                                               const uint64_t* __restrict__ ninv,
                                               const uint64_t* __restrict__ ninv_s) {
-  constexpr int C = 1 << LOGC;
-  constexpr int LT = LOGC / 2;
-  constexpr int TPC = 1 << LT;
-  constexpr int LE = LOGC - LT;
-  constexpr int EPT = 1 << LE;
-  const double qd = (double)q, qinv = 1.0 / qd;
-  auto twv = [&](int k) { return FP ? f2b(Wf[k]) : W[k]; };
-  auto tws = [&](int k) { return FP ? (uint64_t)0 : Ws[k]; };
-  const int tid = threadIdx.x;
-  // column pass: consecutive threads = consecutive columns (coalesced rows);
-  // row pass: consecutive threads = consecutive elements of one chunk
-  const int col = ROW ? tid / TPC : tid % COLS;
-  const int r = ROW ? tid % TPC : tid / COLS;
-  const int unit = blockIdx.x * COLS + col;           // column index j0 or chunk index
-  const int stride = ROW ? 1 : (N >> LOGC);           // element step inside the sub-transform
-  uint64_t* g = ROW ? a + (size_t)unit * C : a + unit;
-  // global twiddle index of group i at local stage st
-  auto twi = [&](int st, int i) { return ROW ? ((N >> LOGC) << st) + unit * (1 << st) + i : (1 << st) + i; };
-  // LDS element index of element e of this unit
-  auto sidx = [&](int e) { return ROW ? col * (C + TPC) + e + e / EPT : e * COLS + col + (e / EPT) * COLS; };
+  typedef PassGeo<LOGC, COLS> G;
+  constexpr int TPC = G::TPC, EPT = G::EPT;
+  const Place<LOGC, COLS, ROW> p(threadIdx.x, blockIdx.x);
   uint64_t x[EPT];
-
   if (!INV) {
-    // ---- load strided: x[u] = element r + TPC u
 #pragma unroll
-    for (int u = 0; u < EPT; ++u) x[u] = FP && !ROW ? to_fbits(g[(size_t)(r + TPC * u) * stride]) : g[(size_t)(r + TPC * u) * stride];
-    // ---- stages 0..LE-1 (t >= TPC) in registers
-    {
-      uint64_t w[EPT], ws[EPT];
-#pragma unroll
-      for (int st = 0; st < LE; ++st)
-#pragma unroll
-        for (int i = 0; i < (1 << st); ++i) {
-          int k = twi(st, i);
-          w[(1 << st) + i - 1] = twv(k);
-          ws[(1 << st) + i - 1] = tws(k);
-        }
-#pragma unroll
-      for (int st = 0; st < LE; ++st) {
-        const int tu = EPT >> (st + 1);
-#pragma unroll
-        for (int u = 0; u < EPT; ++u)
-          if ((u & tu) == 0) {
-            const int i = u / (2 * tu);
-            bfly_fwd<FP>(x[u], x[u + tu], w[(1 << st) + i - 1], ws[(1 << st) + i - 1], q, qd, qinv,
-                         (st & 1) || st == LOGC - 1);
-          }
-      }
+    for (int u = 0; u < EPT; ++u) {
+      x[u] = a[p.gidx(p.r + TPC * u, log_n)];
+      if (FP && !ROW) x[u] = to_fbits(x[u]);
     }
-    // ---- transpose to the contiguous layout
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) s[sidx(r + TPC * u)] = x[u];
-    __syncthreads();
-#pragma unroll
-    for (int v = 0; v < EPT; ++v) x[v] = s[sidx(r * EPT + v)];
-    // ---- stages LE..LOGC-1 (t < TPC), element r*EPT + v
-    {
-      uint64_t w[EPT], ws[EPT];   // at most EPT - 1 twiddles in these stages
-      int pos = 0;
-#pragma unroll
-      for (int st = LE; st < LOGC; ++st) {
-        const int t = C >> (st + 1);
-        const int ng = EPT / (2 * t) > 0 ? EPT / (2 * t) : 1;   // groups touched by this thread
-#pragma unroll
-        for (int gi = 0; gi < ng; ++gi) {
-          int i = (r * EPT) / (2 * t) + gi;
-          int k = twi(st, i);
-          w[pos] = twv(k);
-          ws[pos] = tws(k);
-          ++pos;
-        }
-      }
-      pos = 0;
-#pragma unroll
-      for (int st = LE; st < LOGC; ++st) {
-        const int t = C >> (st + 1);
-        const int ng = EPT / (2 * t) > 0 ? EPT / (2 * t) : 1;
-#pragma unroll
-        for (int v = 0; v < EPT; ++v)
-          if ((v & t) == 0) {
-            const int gi = v / (2 * t);
-            bfly_fwd<FP>(x[v], x[v + t], w[pos + gi], ws[pos + gi], q, qd, qinv, (st & 1) || st == LOGC - 1);
-          }
-        pos += ng;
-      }
-    }
-    if (FP && ROW) {
-#pragma unroll
-      for (int v = 0; v < EPT; ++v) x[v] = from_fbits(f2b(canon(b2f(x[v]), qd)));
-    }
-    if (!FP && ROW) {
-#pragma unroll
-      for (int v = 0; v < EPT; ++v) x[v] = canon4(x[v], q);
-    }
+    fwd_core<LOGC, COLS, ROW, FP>(x, s, p, t, log_n);
     if (ROW) {
-      // back to the strided layout for a coalesced store
+      // residues, back in the strided layout for a coalesced store
+#pragma unroll
+      for (int v = 0; v < EPT; ++v) x[v] = FP ? from_fbits(f2b(canon(b2f(x[v]), t.qd))) : canon8(x[v], t.c, t.q);
       __syncthreads();
 #pragma unroll
-      for (int v = 0; v < EPT; ++v) s[sidx(r * EPT + v)] = x[v];
+      for (int v = 0; v < EPT; ++v) s[p.sidx(p.r * EPT + v)] = x[v];
       __syncthreads();
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) g[(size_t)(r + TPC * u) * stride] = s[sidx(r + TPC * u)];
+      for (int u = 0; u < EPT; ++u) a[p.gidx(p.r + TPC * u, log_n)] = s[p.sidx(p.r + TPC * u)];
     } else {
 #pragma unroll
-      for (int v = 0; v < EPT; ++v) g[(size_t)(r * EPT + v) * stride] = x[v];
+      for (int v = 0; v < EPT; ++v) a[p.gidx(p.r * EPT + v, log_n)] = x[v];
     }
   } else {
-    // ---- inverse: load in the contiguous layout
     if (ROW) {
+      // coalesced load, then the contiguous layout
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) s[sidx(r + TPC * u)] = g[(size_t)(r + TPC * u) * stride];
+      for (int u = 0; u < EPT; ++u) s[p.sidx(p.r + TPC * u)] = a[p.gidx(p.r + TPC * u, log_n)];
       __syncthreads();
 #pragma unroll
-      for (int v = 0; v < EPT; ++v) x[v] = s[sidx(r * EPT + v)];
+      for (int v = 0; v < EPT; ++v) {
+        x[v] = s[p.sidx(p.r * EPT + v)];
+        if (FP) x[v] = to_fbits(x[v]);
+      }
       __syncthreads();
     } else {
 #pragma unroll
-      for (int v = 0; v < EPT; ++v) x[v] = g[(size_t)(r * EPT + v) * stride];
+      for (int v = 0; v < EPT; ++v) x[v] = a[p.gidx(p.r * EPT + v, log_n)];
     }
-    if (FP && ROW) {
-#pragma unroll
-      for (int v = 0; v < EPT; ++v) x[v] = to_fbits(x[v]);
-    }
-    // ---- stages LOGC-1..LE (t < TPC) in registers
-    {
-      uint64_t w[EPT], ws[EPT];   // at most EPT - 1 twiddles in these stages
-      int pos = 0;
-#pragma unroll
-      for (int st = LOGC - 1; st >= LE; --st) {
-        const int t = C >> (st + 1);
-        const int ng = EPT / (2 * t) > 0 ? EPT / (2 * t) : 1;
-#pragma unroll
-        for (int gi = 0; gi < ng; ++gi) {
-          int i = (r * EPT) / (2 * t) + gi;
-          int k = twi(st, i);
-          w[pos] = twv(k);
-          ws[pos] = tws(k);
-          ++pos;
-        }
-      }
-      pos = 0;
-#pragma unroll
-      for (int st = LOGC - 1; st >= LE; --st) {
-        const int t = C >> (st + 1);
-        const int ng = EPT / (2 * t) > 0 ? EPT / (2 * t) : 1;
-#pragma unroll
-        for (int v = 0; v < EPT; ++v)
-          if ((v & t) == 0) {
-            const int gi = v / (2 * t);
-            bfly_inv<FP>(x[v], x[v + t], w[pos + gi], ws[pos + gi], q, qd, qinv, ((LOGC - 1 - st) & 1) || st == 0);
-          }
-        pos += ng;
-      }
-    }
-    // ---- transpose to the strided layout
-#pragma unroll
-    for (int v = 0; v < EPT; ++v) s[sidx(r * EPT + v)] = x[v];
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) x[u] = s[sidx(r + TPC * u)];
-    // ---- stages LE-1..0 (t >= TPC)
-    {
-      uint64_t w[EPT], ws[EPT];
-#pragma unroll
-      for (int st = 0; st < LE; ++st)
-#pragma unroll
-        for (int i = 0; i < (1 << st); ++i) {
-          int k = twi(st, i);
-          w[(1 << st) + i - 1] = twv(k);
-          ws[(1 << st) + i - 1] = tws(k);
-        }
-#pragma unroll
-      for (int st = LE - 1; st >= 0; --st) {
-        const int tu = EPT >> (st + 1);
-#pragma unroll
-        for (int u = 0; u < EPT; ++u)
-          if ((u & tu) == 0) {
-            const int i = u / (2 * tu);
-            bfly_inv<FP>(x[u], x[u + tu], w[(1 << st) + i - 1], ws[(1 << st) + i - 1], q, qd, qinv,
-                         ((LOGC - 1 - st) & 1) || st == 0);
-          }
-      }
-    }
+    inv_core<LOGC, COLS, ROW, FP>(x, s, p, t, log_n);
     if (!ROW) {
       const uint64_t ni = ninv[mi], nis = ninv_s[mi];
       const double nid = (double)ni;
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) x[u] = FP ? f2b(fmulmod(b2f(x[u]), nid, qd, qinv)) : mul_shoup(x[u], ni, nis, q);
-    }
-    if (FP && !ROW) {
-#pragma unroll
-      for (int u = 0; u < EPT; ++u) x[u] = from_fbits(x[u]);
+      for (int u = 0; u < EPT; ++u)
+        x[u] = FP ? from_fbits(f2b(fmulmod(b2f(x[u]), nid, t.qd, t.qinv))) : mul_shoup(x[u], ni, nis, t.q);
     }
 #pragma unroll
-    for (int u = 0; u < EPT; ++u) g[(size_t)(r + TPC * u) * stride] = x[u];
+    for (int u = 0; u < EPT; ++u) a[p.gidx(p.r + TPC * u, log_n)] = x[u];
   }
 }
 
@@ -298,24 +102,18 @@ __global__ __launch_bounds__((1 << (LOGC / 2)) * COLS) void k_ntt_pass(
     uint64_t* __restrict__ base, int log_n, LimbMap map, size_t poly_stride, const uint64_t* __restrict__ tw,
     const uint64_t* __restrict__ tws, const double* __restrict__ twf, const Mod* __restrict__ mods,
     const uint64_t* __restrict__ ninv, const uint64_t* __restrict__ ninv_s, int skip_alpha, int skip_q) {
-  constexpr int C = 1 << LOGC;
-  constexpr int TPC = 1 << (LOGC / 2);
-  // one pad word per EPT elements (row pass) or one group width per EPT rows
-  // (column pass) keeps the contiguous-layout accesses off a single bank set
-  __shared__ uint64_t s[COLS * (C + TPC)];
+  __shared__ uint64_t s[PassGeo<LOGC, COLS>::LDS_WORDS];
   const int limb = blockIdx.y, poly = blockIdx.z;
   if (skip_limb(limb, poly, skip_alpha, skip_q)) return;
-  const int N = 1 << log_n;
   const int mi = lm_mod(map, limb);
-  const uint64_t q = mods[mi].q;
-  uint64_t* a = base + poly * poly_stride + (size_t)limb * N;
-  const uint64_t* W = tw + (size_t)mi * N;
-  const uint64_t* Ws = tws + (size_t)mi * N;
-  const double* Wf = twf + (size_t)mi * N;
-  if (q > (1ull << 49) && q < (1ull << 50))
-    ntt_pass_body<LOGC, COLS, INV, ROW, true>(s, a, W, Ws, Wf, q, N, mi, ninv, ninv_s);
+  const Mod m = cld(mods + mi);
+  const uint64_t q = m.q;
+  uint64_t* a = base + poly * poly_stride + ((size_t)limb << log_n);
+  const Tw t = make_tw(tw, tws, twf, q, m.qinv, mi, log_n);
+  if (fp_prime(q))
+    ntt_pass_body<LOGC, COLS, INV, ROW, true>(s, a, t, log_n, mi, ninv, ninv_s);
   else
-    ntt_pass_body<LOGC, COLS, INV, ROW, false>(s, a, W, Ws, Wf, q, N, mi, ninv, ninv_s);
+    ntt_pass_body<LOGC, COLS, INV, ROW, false>(s, a, t, log_n, mi, ninv, ninv_s);
 }
 
 // ---- launch selection --------------------------------------------------------
@@ -377,6 +175,26 @@ void ntt_inv(ckks_ctx* c, uint64_t* base, int n_limbs, LimbMap map, int n_polys,
   split(c, l1, l2);
   launch<true, true>(c, l2, c->ntt_cols[1], base, n_limbs, map, n_polys, poly_stride, 0, 0);
   launch<true, false>(c, l1, c->ntt_cols[0], base, n_limbs, map, n_polys, poly_stride, 0, 0);
+  HIPCHECK(hipGetLastError());
+}
+
+int ntt_mid_log(const ckks_ctx* c) {
+  int l1, l2;
+  split(c, l1, l2);
+  return std::min(l1, 8);   // a fused column pass holds its sources' coefficients in registers
+}
+
+void ntt_fwd_rows(ckks_ctx* c, uint64_t* base, int n_limbs, LimbMap map, int n_polys, size_t poly_stride,
+                  int skip_alpha, int skip_q) {
+  ProfScope ps(c, "ntt");
+  launch<false, true>(c, c->log_n - ntt_mid_log(c), c->ntt_cols[1], base, n_limbs, map, n_polys, poly_stride,
+                      skip_alpha, skip_q);
+  HIPCHECK(hipGetLastError());
+}
+
+void ntt_inv_rows(ckks_ctx* c, uint64_t* base, int n_limbs, LimbMap map, int n_polys, size_t poly_stride) {
+  ProfScope ps(c, "ntt");
+  launch<true, true>(c, c->log_n - ntt_mid_log(c), c->ntt_cols[1], base, n_limbs, map, n_polys, poly_stride, 0, 0);
   HIPCHECK(hipGetLastError());
 }
 

@@ -1,0 +1,314 @@
+// The NTT's butterflies and in-register sub-transforms (device code), shared by the plain passes
+// (ntt.hip) and the passes fused with base conversion (ntt_fused.hip).
+#pragma once
+#include "fpmod.h"
+#include "internal.h"
+#include "ks_common.h"
+
+namespace ficgcn {
+
+// Integer butterflies with lazy reduction (after Harvey, for q < 2^61): inside a forward transform
+// the values lie in [0, 8q), inside an inverse one in [0, 4q).
+//
+// Shoup's product a w mod q for any 64-bit a, with the quotient's estimate cut short: of
+// a ws = a1 s1 2^64 + (a0 s1 + a1 s0) 2^32 + a0 s0 (32-bit halves) only a1 s1 and the high words of
+// the two middle products are kept.  That loses less than 3 of the exact a w / q - a / 2^64, so
+// r = a w - h q lies in [0, 4q): thirteen instructions, where the exact high product takes twenty.
+// The 64-bit additions below go through v_lshl_add_u64: negated constants are kept opaque and
+// differences are sums with a complement, since a borrow chain (v_sub_co, v_subb_co) and a compare
+// with its selects take more instructions and wait states between them.
+struct IntQ {
+  uint64_t nq;     // -q
+  uint64_t q4;     // 4q
+  uint64_t nq4;    // -4q
+  uint64_t q4p1;   // 4q + 1
+};
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32);
+}
+__device__ __forceinline__ uint64_t opaque(uint64_t v) {
+  v = uniform64(v);
+  asm("" : "+s"(v));
+  return v;
+}
+__device__ __forceinline__ IntQ make_intq(uint64_t q) {
+  return IntQ{opaque(0 - q), 4 * q, opaque(0 - 4 * q), opaque(4 * q + 1)};
+}
+__device__ __forceinline__ uint64_t mul_shoup_lazy4(uint64_t a, uint64_t w, uint64_t ws, const IntQ& c) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), s0 = (uint32_t)ws, s1 = (uint32_t)(ws >> 32);
+  const uint32_t t1 = __umulhi(a0, s1), t2 = __umulhi(a1, s0);
+  uint64_t h = (uint64_t)a1 * s1 + t1, cy;
+  // h += t2 as a multiply-add (a 64-bit addition of a 32-bit word needs a zero half of its own)
+  asm("v_mad_u64_u32 %0, %1, %2, 1, %0" : "+v"(h), "=s"(cy) : "v"(t2));
+  // a w + h (-q) mod 2^64: the cross products' low words, then two multiply-adds
+  const uint32_t w0 = (uint32_t)w, w1 = (uint32_t)(w >> 32), h0 = (uint32_t)h, h1 = (uint32_t)(h >> 32);
+  const uint32_t n0 = (uint32_t)c.nq, n1 = (uint32_t)(c.nq >> 32);
+  const uint32_t x = a0 * w1 + a1 * w0 + (h0 * n1 + h1 * n0);
+  return (uint64_t)h0 * n0 + ((uint64_t)a0 * w0 + ((uint64_t)x << 32));
+}
+// -1 - v, kept apart from the addition that follows
+__device__ __forceinline__ uint64_t cpl(uint64_t v) {
+  v = ~v;
+  asm("" : "+v"(v));
+  return v;
+}
+// x in [0, 2m) -> [0, m) for m < 2^63, nm = -m: the difference's sign as a mask
+__device__ __forceinline__ uint64_t csub(uint64_t x, uint64_t m, uint64_t nm) {
+  const uint64_t d = x + nm;
+  uint32_t k;
+  asm("v_ashrrev_i32 %0, 31, %1" : "=v"(k) : "v"((uint32_t)(d >> 32)));
+  return d + ((uint64_t)(k & (uint32_t)m) | ((uint64_t)(k & (uint32_t)(m >> 32)) << 32));
+}
+//   forward CT: x <- x mod 4q, t = y w in [0, 4q), (x, y) <- (x + t, x - t + 4q), both in [0, 8q);
+//   inverse GS: (x, y) <- (x + y reduced to [0, 4q), (x - y + 4q) w in [0, 4q)).
+// The forward transform's last pass and the inverse's scaling by 1/N return [0, q).
+__device__ __forceinline__ void bf_fwd(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, const IntQ& c) {
+  const uint64_t a = csub(x, c.q4, c.nq4);
+  const uint64_t t = mul_shoup_lazy4(y, w, ws, c);
+  x = a + t;
+  y = a + c.q4p1 + cpl(t);
+}
+__device__ __forceinline__ void bf_inv(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, const IntQ& c) {
+  const uint64_t d = x + c.q4p1 + cpl(y);
+  x = csub(x + y, c.q4, c.nq4);
+  y = mul_shoup_lazy4(d, w, ws, c);
+}
+// [0, 8q) -> [0, q)
+__device__ __forceinline__ uint64_t canon8(uint64_t x, const IntQ& c, uint64_t q) {
+  x = csub(x, c.q4, c.nq4);
+  x = csub(x, 2 * q, 2 * c.nq);
+  return csub(x, q, c.nq);
+}
+
+// fp64 butterflies: sums are brought back to (-q, q) on some stages only (red).  With values in
+// (-c q, c q) a product lands in (-(1/2 + 3c/8) q, (1/2 + 3c/8) q) (fpmod.h's estimate error, q < 2^50),
+// so from c = 1 a forward transform's four unreduced stages reach 1.9, 3.1, 4.8 and 7.1, and an
+// inverse one's three reach 2, 4 and 8: every value an integer of at most 2^53, exact, and every
+// product's operand below 8q.
+__device__ __forceinline__ constexpr bool red_fwd(int st, int logc) { return (st & 3) == 3 || st == logc - 1; }
+__device__ __forceinline__ constexpr bool red_inv(int st, int logc) { return (logc - 1 - st) % 3 == 2 || st == 0; }
+
+template <bool FP>
+__device__ __forceinline__ void bfly_fwd(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, const IntQ& c, double qd,
+                                         double qinv, bool red) {
+  if (FP) {
+    const double xd = b2f(x), v = fmulmod_s(b2f(y), b2f(w), qd, qinv);
+    x = f2b(red ? sred(xd + v, qd, qinv) : xd + v);
+    y = f2b(red ? sred(xd - v, qd, qinv) : xd - v);
+  } else {
+    bf_fwd(x, y, w, ws, c);
+  }
+}
+
+template <bool FP>
+__device__ __forceinline__ void bfly_inv(uint64_t& x, uint64_t& y, uint64_t w, uint64_t ws, const IntQ& c, double qd,
+                                         double qinv, bool red) {
+  if (FP) {
+    const double xd = b2f(x), yd = b2f(y);
+    x = f2b(red ? sred(xd + yd, qd, qinv) : xd + yd);
+    y = f2b(fmulmod_s(red ? sred(xd - yd, qd, qinv) : xd - yd, b2f(w), qd, qinv));
+  } else {
+    bf_inv(x, y, w, ws, c);
+  }
+}
+
+// Shape of one pass: sub-transforms of C points, TPC threads each, EPT points a thread.
+template <int LOGC, int COLS>
+struct PassGeo {
+  static constexpr int C = 1 << LOGC;
+  static constexpr int LT = LOGC / 2;
+  static constexpr int TPC = 1 << LT;
+  static constexpr int LE = LOGC - LT;
+  static constexpr int EPT = 1 << LE;
+  static constexpr int THREADS = TPC * COLS;
+  // one pad word per EPT elements (row pass) or one group width per EPT rows
+  // (column pass) keeps the contiguous-layout accesses off a single bank set
+  static constexpr int LDS_WORDS = COLS * (C + TPC);
+};
+
+// A prime's twiddles: forward (psi) or inverse (ipsi) rows of the context's tables
+struct Tw {
+  const uint64_t* W;
+  const uint64_t* Ws;
+  const double* Wf;
+  uint64_t q;
+  double qd, qinv;
+  IntQ c;
+};
+__device__ __forceinline__ Tw make_tw(const uint64_t* tw, const uint64_t* tws, const double* twf, uint64_t q,
+                                      double qinv, int mi, int log_n) {
+  const size_t o = (size_t)mi << log_n;
+  return Tw{tw + o, tws + o, twf + o, q, (double)q, qinv, make_intq(q)};
+}
+// primes that take the fp64 residue arithmetic
+__device__ __forceinline__ bool fp_prime(uint64_t q) { return q > (1ull << 49) && q < (1ull << 50); }
+
+// A thread's part of a pass: row r of sub-transform `col` of the workgroup, which is column or
+// chunk `unit` of the limb.
+// Column pass: consecutive threads = consecutive columns (coalesced rows); row pass: consecutive
+// threads = consecutive elements of one chunk.
+template <int LOGC, int COLS, bool ROW>
+struct Place {
+  typedef PassGeo<LOGC, COLS> G;
+  int col, r, unit;
+  __device__ __forceinline__ Place(int tid, int block)
+      : col(ROW ? tid / G::TPC : tid % COLS), r(ROW ? tid % G::TPC : tid / COLS), unit(block * COLS + col) {}
+  // LDS word of element e of this unit
+  __device__ __forceinline__ int sidx(int e) const {
+    return ROW ? col * (G::C + G::TPC) + e + e / G::EPT : e * COLS + col + (e / G::EPT) * COLS;
+  }
+  // word of element e inside the limb
+  __device__ __forceinline__ uint32_t gidx(int e, int log_n) const {
+    return ROW ? (uint32_t)unit * G::C + e : ((uint32_t)e << (log_n - LOGC)) + unit;
+  }
+  // twiddle of group i at local stage st
+  __device__ __forceinline__ int twi(int st, int i, int log_n) const {
+    return ROW ? (1 << (log_n - LOGC + st)) + unit * (1 << st) + i : (1 << st) + i;
+  }
+};
+
+// Forward stages of one sub-transform: x in the strided layout (element r + TPC u) on entry, in
+// the contiguous layout (element r EPT + v) on return.  `s` is free on entry.
+template <int LOGC, int COLS, bool ROW, bool FP, int E>
+__device__ __forceinline__ void fwd_core(uint64_t (&x)[E], uint64_t* s,
+                                         const Place<LOGC, COLS, ROW>& p, const Tw& t, int log_n) {
+  typedef PassGeo<LOGC, COLS> G;
+  constexpr int C = G::C, TPC = G::TPC, LE = G::LE, EPT = G::EPT;
+  static_assert(E == EPT, "one thread's points");
+  auto twv = [&](int k) { return FP ? f2b(t.Wf[k]) : t.W[k]; };
+  auto tws = [&](int k) { return FP ? (uint64_t)0 : t.Ws[k]; };
+  // stages 0..LE-1 (butterfly distance >= TPC) in registers
+  {
+    uint64_t w[EPT], ws[EPT];
+#pragma unroll
+    for (int st = 0; st < LE; ++st)
+#pragma unroll
+      for (int i = 0; i < (1 << st); ++i) {
+        const int k = p.twi(st, i, log_n);
+        w[(1 << st) + i - 1] = twv(k);
+        ws[(1 << st) + i - 1] = tws(k);
+      }
+#pragma unroll
+    for (int st = 0; st < LE; ++st) {
+      const int tu = EPT >> (st + 1);
+#pragma unroll
+      for (int u = 0; u < EPT; ++u)
+        if ((u & tu) == 0) {
+          const int i = u / (2 * tu);
+          bfly_fwd<FP>(x[u], x[u + tu], w[(1 << st) + i - 1], ws[(1 << st) + i - 1], t.c, t.qd, t.qinv,
+                       red_fwd(st, LOGC));
+        }
+    }
+  }
+  // transpose to the contiguous layout
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) s[p.sidx(p.r + TPC * u)] = x[u];
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < EPT; ++v) x[v] = s[p.sidx(p.r * EPT + v)];
+  // stages LE..LOGC-1 (butterfly distance < TPC)
+  {
+    uint64_t w[EPT], ws[EPT];   // at most EPT - 1 twiddles in these stages
+    int pos = 0;
+#pragma unroll
+    for (int st = LE; st < LOGC; ++st) {
+      const int d = C >> (st + 1);
+      const int ng = EPT / (2 * d) > 0 ? EPT / (2 * d) : 1;   // groups touched by this thread
+#pragma unroll
+      for (int gi = 0; gi < ng; ++gi) {
+        const int k = p.twi(st, (p.r * EPT) / (2 * d) + gi, log_n);
+        w[pos] = twv(k);
+        ws[pos] = tws(k);
+        ++pos;
+      }
+    }
+    pos = 0;
+#pragma unroll
+    for (int st = LE; st < LOGC; ++st) {
+      const int d = C >> (st + 1);
+      const int ng = EPT / (2 * d) > 0 ? EPT / (2 * d) : 1;
+#pragma unroll
+      for (int v = 0; v < EPT; ++v)
+        if ((v & d) == 0) {
+          const int gi = v / (2 * d);
+          bfly_fwd<FP>(x[v], x[v + d], w[pos + gi], ws[pos + gi], t.c, t.qd, t.qinv, red_fwd(st, LOGC));
+        }
+      pos += ng;
+    }
+  }
+}
+
+// Inverse stages of one sub-transform: contiguous layout on entry, strided on return (not scaled
+// by 1/N).  `s` is free on entry.
+template <int LOGC, int COLS, bool ROW, bool FP, int E>
+__device__ __forceinline__ void inv_core(uint64_t (&x)[E], uint64_t* s,
+                                         const Place<LOGC, COLS, ROW>& p, const Tw& t, int log_n) {
+  typedef PassGeo<LOGC, COLS> G;
+  constexpr int C = G::C, TPC = G::TPC, LE = G::LE, EPT = G::EPT;
+  static_assert(E == EPT, "one thread's points");
+  auto twv = [&](int k) { return FP ? f2b(t.Wf[k]) : t.W[k]; };
+  auto tws = [&](int k) { return FP ? (uint64_t)0 : t.Ws[k]; };
+  // stages LOGC-1..LE (butterfly distance < TPC) in registers
+  {
+    uint64_t w[EPT], ws[EPT];   // at most EPT - 1 twiddles in these stages
+    int pos = 0;
+#pragma unroll
+    for (int st = LOGC - 1; st >= LE; --st) {
+      const int d = C >> (st + 1);
+      const int ng = EPT / (2 * d) > 0 ? EPT / (2 * d) : 1;
+#pragma unroll
+      for (int gi = 0; gi < ng; ++gi) {
+        const int k = p.twi(st, (p.r * EPT) / (2 * d) + gi, log_n);
+        w[pos] = twv(k);
+        ws[pos] = tws(k);
+        ++pos;
+      }
+    }
+    pos = 0;
+#pragma unroll
+    for (int st = LOGC - 1; st >= LE; --st) {
+      const int d = C >> (st + 1);
+      const int ng = EPT / (2 * d) > 0 ? EPT / (2 * d) : 1;
+#pragma unroll
+      for (int v = 0; v < EPT; ++v)
+        if ((v & d) == 0) {
+          const int gi = v / (2 * d);
+          bfly_inv<FP>(x[v], x[v + d], w[pos + gi], ws[pos + gi], t.c, t.qd, t.qinv, red_inv(st, LOGC));
+        }
+      pos += ng;
+    }
+  }
+  // transpose to the strided layout
+#pragma unroll
+  for (int v = 0; v < EPT; ++v) s[p.sidx(p.r * EPT + v)] = x[v];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) x[u] = s[p.sidx(p.r + TPC * u)];
+  // stages LE-1..0 (butterfly distance >= TPC)
+  {
+    uint64_t w[EPT], ws[EPT];
+#pragma unroll
+    for (int st = 0; st < LE; ++st)
+#pragma unroll
+      for (int i = 0; i < (1 << st); ++i) {
+        const int k = p.twi(st, i, log_n);
+        w[(1 << st) + i - 1] = twv(k);
+        ws[(1 << st) + i - 1] = tws(k);
+      }
+#pragma unroll
+    for (int st = LE - 1; st >= 0; --st) {
+      const int tu = EPT >> (st + 1);
+#pragma unroll
+      for (int u = 0; u < EPT; ++u)
+        if ((u & tu) == 0) {
+          const int i = u / (2 * tu);
+          bfly_inv<FP>(x[u], x[u + tu], w[(1 << st) + i - 1], ws[(1 << st) + i - 1], t.c, t.qd, t.qinv,
+                       red_inv(st, LOGC));
+        }
+    }
+  }
+}
+
+}  // namespace ficgcn

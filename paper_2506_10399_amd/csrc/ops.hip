@@ -6,19 +6,12 @@
 //   key         [beta][2][L+alpha][N]  switching key over every prime
 // One thread owns one coefficient index j of one limb, so every access of a
 // warp is 64 consecutive words.
-#include "internal.h"
+#include "ks_common.h"
+#include "ntt_fused.h"
 
 namespace ficgcn {
 
 constexpr int EW = 256;
-
-__device__ __forceinline__ uint32_t auto_index(uint32_t k, uint64_t g, int log_n) {
-  // evaluation index k holds A(psi^(2 brev(k) + 1)); sigma_g reads the index of psi^(g (2 brev(k) + 1))
-  uint32_t N2 = 2u << log_n;
-  uint32_t e = 2u * bitrev(k, log_n) + 1u;
-  uint32_t ge = (uint32_t)(((uint64_t)e * g) & (N2 - 1));
-  return bitrev((ge - 1u) >> 1, log_n);
-}
 
 __global__ void k_pmul_acc(uint64_t* __restrict__ acc, PtrList cts, PtrList pts, int k, int n_limbs, int log_n,
                            const Mod* __restrict__ mods) {
@@ -82,7 +75,7 @@ __global__ void k_automorph(uint64_t* __restrict__ out, const uint64_t* __restri
   const size_t N = (size_t)1 << log_n;
   const uint32_t j = blockIdx.x * EW + threadIdx.x;
   const size_t base = ((size_t)blockIdx.z * n_limbs + blockIdx.y) * N;
-  out[base + j] = in[base + auto_index(j, g, log_n)];
+  out[base + j] = in[base + auto_idx(j, g, log_n)];
 }
 
 void automorph_ntt(ckks_ctx* c, uint64_t* out, const uint64_t* in, uint64_t g, int n_limbs, int n_polys) {
@@ -135,6 +128,10 @@ void modup(ckks_ctx* c, const uint64_t* a_ntt, int level, uint64_t* D, uint64_t*
   const int l1 = level + 1, ext = l1 + c->alpha;
   const int nd = (l1 + c->alpha - 1) / c->alpha;
   if (!tmp) tmp = (uint64_t*)c->buf(S_MODUP_TMP, (size_t)l1 * N * 8);
+  if (fused_basis(c)) {
+    modup_polys(c, level, nullptr, a_ntt, 1, tmp, D);
+    return;
+  }
   HIPCHECK(hipMemcpyAsync(tmp, a_ntt, (size_t)l1 * N * 8, hipMemcpyDeviceToDevice, c->stream));
   ntt_inv(c, tmp, l1, lm_q(l1), 1, 0);
   for (int d = 0; d < nd; ++d) {
@@ -158,7 +155,7 @@ __global__ void k_keymac(uint64_t* __restrict__ acc, const uint64_t* __restrict_
   const uint32_t j = blockIdx.x * EW + threadIdx.x;
   const int i = blockIdx.y, c = blockIdx.z;
   const int m = i < lvl1 ? i : i - lvl1 + L;
-  const uint32_t jj = g == 1 ? j : auto_index(j, g, log_n);
+  const uint32_t jj = g == 1 ? j : auto_idx(j, g, log_n);
   u128 s = 0;
   for (int d = 0; d < nd; ++d)
     s += (u128)D[((size_t)d * ext + i) * N + jj] * key[(((size_t)d * 2 + c) * n_mod + m) * N + j];
@@ -174,16 +171,10 @@ void keymac(ckks_ctx* c, uint64_t* acc, const uint64_t* D, const uint64_t* key, 
   HIPCHECK(hipGetLastError());
 }
 
-struct MDConst {
-  uint64_t hP[8];
-  uint64_t hQ[64];
-  uint64_t pinv[64], pinv_s[64];
-};
-
 // conv_c[i] = FastBConv_{P->q_i}([x_P + h]_P) - h  (coefficient form)
 __global__ void k_moddown_conv(const uint64_t* __restrict__ accP, size_t acc_ps, const int* __restrict__ src_mod,
                                const int* __restrict__ dst_mod, int ns, int nd, const uint64_t* __restrict__ table,
-                               MDConst k, uint64_t* __restrict__ out, size_t out_ps, int log_n,
+                               const MDK k, uint64_t* __restrict__ out, size_t out_ps, int log_n,
                                const Mod* __restrict__ mods) {
   const size_t N = (size_t)1 << log_n;
   const size_t j = blockIdx.x * (size_t)EW + threadIdx.x;
@@ -205,7 +196,7 @@ __global__ void k_moddown_conv(const uint64_t* __restrict__ accP, size_t acc_ps,
 
 // out_c[i] = (acc_c[i] - conv_c[i]) * P^-1 (+ add_c[i], add0 read through sigma_g when g != 1)
 __global__ void k_moddown_final(const uint64_t* __restrict__ acc, size_t acc_ps, const uint64_t* __restrict__ conv,
-                                size_t conv_ps, MDConst k, uint64_t* __restrict__ out, size_t out_ps,
+                                size_t conv_ps, const MDK k, uint64_t* __restrict__ out, size_t out_ps,
                                 const uint64_t* __restrict__ add0, uint64_t g0, const uint64_t* __restrict__ add1,
                                 int log_n, const Mod* __restrict__ mods) {
   const size_t N = (size_t)1 << log_n;
@@ -214,31 +205,9 @@ __global__ void k_moddown_final(const uint64_t* __restrict__ acc, size_t acc_ps,
   const uint64_t q = mods[i].q;
   uint64_t v = sub_mod(acc[c * acc_ps + i * N + j], conv[c * conv_ps + i * N + j], q);
   v = mul_shoup(v, k.pinv[i], k.pinv_s[i], q);
-  if (c == 0 && add0) v = add_mod(v, add0[i * N + (g0 == 1 ? j : auto_index(j, g0, log_n))], q);
+  if (c == 0 && add0) v = add_mod(v, add0[i * N + (g0 == 1 ? j : auto_idx(j, g0, log_n))], q);
   if (c == 1 && add1) v = add_mod(v, add1[i * N + j], q);
   out[c * out_ps + i * N + j] = v;
-}
-
-static MDConst md_const(ckks_ctx* c, int level) {
-  MDConst k{};
-  if (c->alpha > 8 || level + 1 > 64) FICGCN_THROW(EINVAL_, "too many primes");
-  // h = floor(P / 2) = (P - 1) / 2 (P odd); residues via (P mod m - 1) / 2 computed as
-  // (P - 1)/2 mod m = (P mod m - 1) * 2^-1 mod m
-  for (int t = 0; t < c->alpha; ++t) {
-    uint64_t pm = c->mod[c->L + t];
-    uint64_t P_mod = 1;
-    for (int u = 0; u < c->alpha; ++u) P_mod = (uint64_t)((u128)P_mod * (c->mod[c->L + u] % pm) % pm);
-    k.hP[t] = (uint64_t)((u128)sub_mod(P_mod, 1, pm) * invmod(2, pm) % pm);
-  }
-  for (int i = 0; i <= level; ++i) {
-    uint64_t q = c->mod[i];
-    uint64_t P_mod = 1;
-    for (int u = 0; u < c->alpha; ++u) P_mod = (uint64_t)((u128)P_mod * (c->mod[c->L + u] % q) % q);
-    k.hQ[i] = (uint64_t)((u128)sub_mod(P_mod, 1, q) * invmod(2, q) % q);
-    k.pinv[i] = invmod(P_mod, q);
-    k.pinv_s[i] = shoup(k.pinv[i], q);
-  }
-  return k;
 }
 
 void moddown(ckks_ctx* c, uint64_t* acc, int level, uint64_t* out, const uint64_t* add0, uint64_t g_add0,
@@ -246,12 +215,18 @@ void moddown(ckks_ctx* c, uint64_t* acc, int level, uint64_t* out, const uint64_
   ProfScope ps(c, "moddown");
   const size_t N = c->N;
   const int l1 = level + 1, ext = l1 + c->alpha;
+  if (c->alpha > 8 || l1 > 64) FICGCN_THROW(EINVAL_, "too many primes");
+  const MDK& k = c->mdk[level];
+  if (!conv) conv = (uint64_t*)c->buf(S_MD_TMP, (size_t)2 * l1 * N * 8);
+  if (fused_basis(c)) {
+    moddown_polys(c, level, acc, 2, conv, false);
+    moddown_final(c, level, acc, conv, nullptr, FinalJob{out, add0, add1, g_add0, 0, 0}, 1);
+    return;
+  }
   // P limbs back to coefficient form
   ntt_inv(c, acc + (size_t)l1 * N, c->alpha, LimbMap{c->L, 1 << 30, 0}, 2, (size_t)ext * N);
   const BConv& bc = get_moddown(c, level);
   BConvDev idx = bconv_indices(c, bc, S_IDX_B);
-  MDConst k = md_const(c, level);
-  if (!conv) conv = (uint64_t*)c->buf(S_MD_TMP, (size_t)2 * l1 * N * 8);
   hipLaunchKernelGGL(k_moddown_conv, dim3(N / EW, 2), dim3(EW), 0, c->stream, acc + (size_t)l1 * N, (size_t)ext * N,
                      idx.src_mod, idx.dst_mod, bc.n_src, bc.n_dst, (const uint64_t*)bc.dev, k, conv, (size_t)l1 * N,
                      c->log_n, c->t.mods);
@@ -262,24 +237,8 @@ void moddown(ckks_ctx* c, uint64_t* acc, int level, uint64_t* out, const uint64_
   HIPCHECK(hipGetLastError());
 }
 
-struct RSConst {
-  uint64_t h[64];          // floor(q_l / 2) mod q_i
-  uint64_t inv[64], inv_s[64];
-};
-
-// d_c[i] = (h - ((x_c + h) mod q_l)) mod q_i, x_c = last limb in coefficient form
-__global__ void k_rescale_prep(const uint64_t* __restrict__ last, uint64_t* __restrict__ d, int lvl, uint64_t hl,
-                               RSConst k, int log_n, const Mod* __restrict__ mods) {
-  const size_t N = (size_t)1 << log_n;
-  const size_t j = blockIdx.x * (size_t)EW + threadIdx.x;
-  const int i = blockIdx.y, c = blockIdx.z;
-  const uint64_t ql = mods[lvl].q, q = mods[i].q;
-  uint64_t y = add_mod(last[c * N + j], hl, ql);   // < q_l < q_i (descending chain)
-  d[(c * lvl + i) * N + j] = sub_mod(k.h[i], y, q);
-}
-
 // c'_i = (c_i + d_i) * q_l^-1, compacted from [2][l+1][N] to [2][l][N]; one thread per (j, c)
-__global__ void k_rescale_final(uint64_t* __restrict__ ct, const uint64_t* __restrict__ d, int lvl, RSConst k,
+__global__ void k_rescale_final(uint64_t* __restrict__ ct, const uint64_t* __restrict__ d, int lvl, RSK k,
                                 int log_n, const Mod* __restrict__ mods) {
   const size_t N = (size_t)1 << log_n;
   const size_t j = blockIdx.x * (size_t)EW + threadIdx.x;
@@ -295,24 +254,10 @@ void rescale_inplace(ckks_ctx* c, uint64_t* ct, int level) {
   if (level < 1) FICGCN_THROW(ELEVEL_, "rescale at level 0");
   if (level > 63) FICGCN_THROW(EINVAL_, "too many primes");
   const size_t N = c->N;
-  const int l1 = level + 1;
+  const RSK& k = c->rsk[level];
   uint64_t* last = (uint64_t*)c->buf(S_RS_TMP, 2 * N * 8);
-  HIPCHECK(hipMemcpyAsync(last, ct + (size_t)level * N, N * 8, hipMemcpyDeviceToDevice, c->stream));
-  HIPCHECK(hipMemcpyAsync(last + N, ct + (size_t)(l1 + level) * N, N * 8, hipMemcpyDeviceToDevice, c->stream));
-  ntt_inv(c, last, 1, LimbMap{level, 1 << 30, 0}, 2, N);
-  RSConst k{};
-  uint64_t ql = c->mod[level], hl = ql / 2;
-  for (int i = 0; i < level; ++i) {
-    uint64_t q = c->mod[i];
-    k.h[i] = hl % q;
-    k.inv[i] = invmod(ql % q, q);
-    k.inv_s[i] = shoup(k.inv[i], q);
-  }
   uint64_t* d = (uint64_t*)c->buf(S_RS_D, (size_t)2 * level * N * 8);
-  hipLaunchKernelGGL(k_rescale_prep, dim3(N / EW, level, 2), dim3(EW), 0, c->stream, last, d, level, hl, k, c->log_n,
-                     c->t.mods);
-  HIPCHECK(hipGetLastError());
-  ntt_fwd(c, d, level, lm_q(level), 2, (size_t)level * N);
+  rescale_prep(c, level, nullptr, ct, 1, last, d);
   hipLaunchKernelGGL(k_rescale_final, dim3(N / EW, 2), dim3(EW), 0, c->stream, ct, d, level, k, c->log_n, c->t.mods);
   HIPCHECK(hipGetLastError());
 }
