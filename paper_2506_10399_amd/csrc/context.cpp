@@ -305,6 +305,13 @@ void ensure_device(ckks_ctx* c) {
   up(&c->t.ninv_s, c->h_ninv_s);
   HIPCHECK(hipMalloc(&c->t.mods, c->h_mods.size() * sizeof(Mod)));
   HIPCHECK(hipMemcpy(c->t.mods, c->h_mods.data(), c->h_mods.size() * sizeof(Mod), hipMemcpyHostToDevice));
+  std::vector<Fold25> fold(c->n_mod());
+  for (int m = 0; m < c->n_mod(); ++m) {
+    const uint64_t q = c->mod[m], r25 = (1ull << 25) % q, r50 = (1ull << 50) % q;
+    fold[m] = Fold25{r25, shoup(r25, q), r50, shoup(r50, q), shoup(1, q)};
+  }
+  HIPCHECK(hipMalloc(&c->t.fold25, fold.size() * sizeof(Fold25)));
+  HIPCHECK(hipMemcpy(c->t.fold25, fold.data(), fold.size() * sizeof(Fold25), hipMemcpyHostToDevice));
   // every base-conversion table of the chain, so later calls find them built
   for (int level = 0; level < c->L; ++level) {
     for (int d = 0; d * c->alpha <= level; ++d) get_modup(c, level, d);
@@ -451,6 +458,7 @@ ckks_ctx::~ckks_ctx() {
   if (enc_pos) (void)hipFree(enc_pos);
   if (enc_flag) (void)hipFree(enc_flag);
   if (t.mods) (void)hipFree(t.mods);
+  if (t.fold25) (void)hipFree(t.fold25);
   if (mid_src) (void)hipFree(mid_src);
   if (mid_dst) (void)hipFree(mid_dst);
   for (auto& kv : modup) { (void)hipFree(kv.second.dev); (void)hipFree(kv.second.idx); }

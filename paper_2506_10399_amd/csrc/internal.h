@@ -41,6 +41,11 @@ FICGCN_FD int lm_mod(const LimbMap& m, int i) {
 inline LimbMap lm_q(int n) { return LimbMap{0, n, 0}; }                     // plain Q limbs 0..n-1
 inline LimbMap lm_ext(int level, int L) { return LimbMap{0, level + 1, L - level - 1}; }  // Q_l then P
 
+// 2^25 and 2^50 modulo a prime, Shoup companions of both and of 1: sums kept in 25-bit halves
+struct Fold25 {
+  uint64_t r25, r25_s, r50, r50_s, one_s;
+};
+
 // Device-resident per-modulus tables.
 struct Tables {
   uint64_t* psi = nullptr;     // [n_mod][N] psi^{brev(k)}
@@ -52,6 +57,7 @@ struct Tables {
   Mod* mods = nullptr;         // [n_mod]
   uint64_t* ninv = nullptr;    // [n_mod] N^{-1}
   uint64_t* ninv_s = nullptr;
+  Fold25* fold25 = nullptr;    // [n_mod]
 };
 
 // Fast base conversion constants from a source prime set to a destination set.

@@ -16,11 +16,13 @@
 // grouped final step replaces "write R switched ciphertexts, read them
 // back for a masked sum" by one read of acc and conv per switch.
 #include <algorithm>
+#include <map>
 #include <numeric>
 
 #include "fpmod.h"
 #include "ks_batch.h"
 #include "ks_common.h"
+#include "ntt_dev.h"
 #include "ntt_fused.h"
 
 namespace ficgcn {
@@ -213,6 +215,7 @@ __global__ void k_ks_final(const uint64_t* __restrict__ acc, const uint64_t* __r
 
 enum { S_KB_TMP = 50, S_KB_D, S_KB_ACC, S_KB_CONV, S_KB_JOBS, S_KB_SRC, S_KB_GRP, S_TB_JOBS, S_RS_PTR, S_RS_LAST,
        S_RS_D, S_GM_TERMS, S_GM_START, S_GM_OUT, S_KB_RUNS };
+enum { S_GM_GRP = 89 };
 
 template <typename T>
 static T* upload(ckks_ctx* c, int slot, const std::vector<T>& v) {
@@ -1270,6 +1273,236 @@ __global__ void __launch_bounds__(GM_TB) k_group_mac_np(const MacTermNP* __restr
   }
 }
 
+// ---- the same sums with the ciphertexts in LDS ----------------------------------------------
+// Every giant step reads some of the same few baby-step ciphertexts, each a sixth of them at the
+// 19717-node shape: there the sums above move 55 GB of ciphertext words from L2 for 9 GB of mask
+// words, and L2 bounds them.  Here a workgroup takes 16 coefficients (128-byte runs) of one limb,
+// reads those of every ciphertext into LDS once, as pairs of 25-bit halves, and walks all the
+// groups: eight groups a wave, eight lanes a group, two coefficients a lane, so that a term is one
+// 16-byte mask load and 2 NP 16-byte LDS reads.  With x = x0 + x1 2^25 and p alike, the sums of
+// x0 p0, x1 p1 and (x0 + x1)(p0 + p1) are kept in 64 bits, three multiply-adds a product, no
+// conversion, and reduced once a group (GL_MAX_TERMS bounds the third).  Groups go by falling
+// length, so the eight of a wave end together, and a wave takes the next eight from a counter.
+// Masks are requested eight terms ahead; the term list lies in LDS too, since loads come back in
+// order and waiting for a list entry from memory would wait for every mask requested before it.
+// Odd groups take the two components in the other order: at any time half of a wave reads each half
+// of the LDS banks.
+constexpr int GL_COEF = 16;
+constexpr int GL_MAX_TERMS = 4095;     // 4095 * 2^52 < 2^64
+constexpr int GL_MIN_TERMS = 3000;
+constexpr int GL_T = 768;              // threads: three waves a SIMD, as the registers allow
+// a term: the mask's place, in masks of l1 limbs from the base, and the ciphertext tuple
+constexpr int GL_TUP_BITS = 9;
+constexpr uint32_t GL_TUP = (1u << GL_TUP_BITS) - 1;
+constexpr int GL_CAP = 6144;           // 96 KiB of ciphertext words
+constexpr int GL_LIST = 12288;         // terms: 48 KiB
+struct NpGroup {
+  int32_t start, len, g;   // its terms, its number
+};
+
+// A + B 2^25 + C 2^50 mod q in [0, q) for a prime of the fp64 range.  A word v = v1 2^32 + v0 below 2^63
+// comes back as v1 2^32 (an exact double, its quotient by q below 2^14) brought to (-q, q), plus v0.
+__device__ __forceinline__ uint64_t fold25_fp(uint64_t A, uint64_t B, uint64_t C, double qd, double qinv, const Fold25& f) {
+  auto part = [&](uint64_t v) {
+    return sred((double)(uint32_t)(v >> 32) * 4294967296.0, qd, qinv) + (double)(uint32_t)v;
+  };
+  const double s = part(A) + (fmulmod_s(part(B), (double)f.r25, qd, qinv) + fmulmod_s(part(C), (double)f.r50, qd, qinv));
+  return from_fbits(f2b(canon(sred(s, qd, qinv), qd)));
+}
+
+template <int NP>
+__global__ __launch_bounds__(GL_T) void k_group_mac_lds(
+    const uint64_t* const* __restrict__ tuples, int n_tup, const uint32_t* __restrict__ terms, int n_terms,
+    const NpGroup* __restrict__ groups, int n_groups, const uint64_t* __restrict__ pt_base,
+    uint64_t* const* __restrict__ outs, int l1, int accumulate, int log_n, const Mod* __restrict__ mods,
+    const Fold25* __restrict__ folds) {
+  typedef uint64_t v2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(1))) const v2 gv2;
+  typedef __attribute__((address_space(1))) v2 gv2w;
+  constexpr int T = GL_T;
+  constexpr uint32_t M25 = (1u << 25) - 1;
+  constexpr int U = 4;                 // terms a step; masks are two steps ahead
+  __shared__ v4 sx[GL_CAP];            // [tuple][NP][2 components][8 lanes]
+  __shared__ uint32_t st[GL_LIST];
+  __shared__ int ctr;
+  const size_t N = (size_t)1 << log_n;
+  const int i = blockIdx.y;
+  const size_t j0 = (size_t)blockIdx.x * GL_COEF;
+  auto halves = [](v2 w) {
+    return v4{(uint32_t)w.x & M25, (uint32_t)(w.x >> 25), (uint32_t)w.y & M25, (uint32_t)(w.y >> 25)};
+  };
+  const int units = n_tup * NP * 2 * 8;
+  for (int u = threadIdx.x; u < units; u += T) {
+    const int lane = u & 7, comp = (u >> 3) & 1, tc = u >> 4;
+    sx[u] = halves(*(gv2*)(tuples[tc] + ((size_t)comp * l1 + i) * N + j0 + 2 * lane));
+  }
+  for (int u = threadIdx.x; u < n_terms; u += T) st[u] = terms[u];
+  if (threadIdx.x == 0) ctr = T / 64;
+  __syncthreads();
+  const int team = (threadIdx.x & 63) >> 3, l8 = threadIdx.x & 7;
+  const Mod m = cld(mods + i);
+  const uint64_t q = m.q;
+  const bool fp = fp_prime(q);
+  const double qd = (double)q;
+  const Fold25 f = cld(folds + i);
+  const IntQ iq = make_intq(q);
+  const uint64_t* const mb = pt_base + (size_t)i * N + j0 + 2 * l8;
+  const size_t mask_words = (size_t)l1 * N;
+  const int odd = team & 1;
+  const v4* const sl = sx + l8 + odd * 8;
+  const int swap = odd ? -8 : 8;       // from a tuple's first component read to the other
+  const int n_oct = (n_groups + 7) >> 3;
+  auto mask = [&](uint32_t e) {
+    return __builtin_nontemporal_load((gv2*)(mb + (size_t)(e >> GL_TUP_BITS) * mask_words));
+  };
+  int oct = threadIdx.x >> 6;
+  while (oct < n_oct) {
+    const int gi = oct * 8 + team;
+    const NpGroup gd = gi < n_groups ? groups[gi] : NpGroup{0, 0, -1};
+    // the longest of the eight (they go by falling length): the first
+    const int n = __builtin_amdgcn_readfirstlane(groups[oct * 8].len);
+    // a lane past its group's end repeats an entry (its last; the list's first where it has none)
+    // and takes 0 for the mask
+    const int first = gd.len > 0 ? gd.start : 0, last = gd.len > 0 ? gd.start + gd.len - 1 : 0;
+    auto entry = [&](int t) { return st[first + t < last ? first + t : last]; };
+    uint64_t A[NP][4], B[NP][4], C[NP][4];
+#pragma unroll
+    for (int c = 0; c < NP; ++c)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) A[c][k] = B[c][k] = C[c][k] = 0;
+    uint32_t e[3][U];
+    v2 p[3][U];
+    // step s of the term loop uses e and p of slot s mod 3
+    if (n > 0) {
+#pragma unroll
+      for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int u = 0; u < U; ++u) e[s][u] = entry(s * U + u);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int u = 0; u < U; ++u) p[s][u] = mask(e[s][u]);
+    }
+    auto step = [&](uint32_t (&ec)[U], v2 (&pc)[U], uint32_t (&en)[U], v2 (&pn)[U], int t) {
+      // the masks two steps on, then this step's products, then the entries three steps on
+#pragma unroll
+      for (int u = 0; u < U; ++u) pn[u] = mask(en[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v2 pw = pc[u];
+        if (t + u >= gd.len) pw = v2{0, 0};
+        const v4 h = halves(pw);
+        const uint32_t hs = h.x + h.y, ht = h.z + h.w;
+        const v4* x = sl + (ec[u] & GL_TUP) * (NP * 16);
+#pragma unroll
+        for (int c = 0; c < NP; ++c)
+#pragma unroll
+          for (int comp = 0; comp < 2; ++comp) {
+            const v4 w = x[c * 16 + (comp ? swap : 0)];
+            const int k = comp * 2;
+            A[c][k] += (uint64_t)w.x * h.x;
+            C[c][k] += (uint64_t)w.y * h.y;
+            B[c][k] += (uint64_t)(w.x + w.y) * hs;
+            A[c][k + 1] += (uint64_t)w.z * h.z;
+            C[c][k + 1] += (uint64_t)w.w * h.w;
+            B[c][k + 1] += (uint64_t)(w.z + w.w) * ht;
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) ec[u] = entry(t + 3 * U + u);
+    };
+    if (n > 0)
+      for (int t = 0;;) {
+        step(e[0], p[0], e[2], p[2], t);
+        if ((t += U) >= n) break;
+        step(e[1], p[1], e[0], p[0], t);
+        if ((t += U) >= n) break;
+        step(e[2], p[2], e[1], p[1], t);
+        if ((t += U) >= n) break;
+      }
+    if (gd.g >= 0) {
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {
+        uint64_t* out = outs[(size_t)gd.g * NP + c] + (size_t)i * N + j0 + 2 * l8;
+        uint64_t r[4];
+        if (fp) {
+#pragma unroll
+          for (int w = 0; w < 4; ++w)
+            r[w] = fold25_fp(A[c][w], B[c][w] - A[c][w] - C[c][w], C[c][w], qd, m.qinv, f);
+        } else {
+          // A + B 2^25 + C 2^50, each part lazily to [0, 4q)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const uint64_t v = mul_shoup_lazy4(A[c][w], 1, f.one_s, iq) +
+                               mul_shoup_lazy4(B[c][w] - A[c][w] - C[c][w], f.r25, f.r25_s, iq);
+            r[w] = canon8(csub(v, iq.q4, iq.nq4) + mul_shoup_lazy4(C[c][w], f.r50, f.r50_s, iq), iq, q);
+          }
+        }
+#pragma unroll
+        for (int comp = 0; comp < 2; ++comp) {
+          uint64_t* o = out + (size_t)(comp ^ odd) * mask_words;
+          v2 v = {r[comp * 2], r[comp * 2 + 1]};
+          if (accumulate) {
+            const v2 old = *(gv2*)o;
+            v.x = add_mod(v.x, old.x, q);
+            v.y = add_mod(v.y, old.y, q);
+          }
+          *(gv2w*)o = v;
+        }
+      }
+    }
+    if ((threadIdx.x & 63) == 0) oct = atomicAdd(&ctr, 1);
+    oct = __builtin_amdgcn_readfirstlane(oct);
+  }
+}
+
+// One launch's groups as the LDS form reads them: as many of groups[g0..) as its tables hold, in the
+// order of falling length.  Returns the first group left, or g0 where the form does not apply: one
+// group's terms or distinct ciphertext tuples beyond the tables, terms without a mask, masks that are
+// not whole masks apart.
+struct LdsForm {
+  std::vector<const uint64_t*> tuples;
+  std::vector<uint32_t> terms;
+  std::vector<NpGroup> groups;
+  const uint64_t* base = nullptr;
+};
+static size_t lds_form(ckks_ctx* c, int level, int np, const std::vector<std::vector<MacTermNP>>& groups, size_t g0,
+                       LdsForm& f) {
+  const size_t mask_words = (size_t)(level + 1) * c->N;
+  for (const auto& g : groups)
+    for (const MacTermNP& t : g)
+      if (t.pt && (!f.base || t.pt < f.base)) f.base = t.pt;
+  std::map<std::vector<const uint64_t*>, uint32_t> seen;
+  size_t g1 = g0;
+  for (; g1 < groups.size(); ++g1) {
+    const auto& g = groups[g1];
+    if (g.size() > (size_t)GL_MAX_TERMS || f.terms.size() + g.size() > (size_t)GL_LIST) break;
+    const size_t start = f.terms.size();
+    bool fits = true;
+    for (const MacTermNP& t : g) {
+      const size_t w = (size_t)(t.pt - f.base);
+      if (!t.pt || w % mask_words || w / mask_words >= (1u << (32 - GL_TUP_BITS))) return g0;
+      const std::vector<const uint64_t*> key(t.ct, t.ct + np);
+      auto it = seen.find(key);
+      if (it == seen.end()) {
+        fits = (seen.size() + 1) * np * 16 <= (size_t)GL_CAP && seen.size() < GL_TUP;
+        if (!fits) break;
+        it = seen.emplace(key, (uint32_t)seen.size()).first;
+        f.tuples.insert(f.tuples.end(), key.begin(), key.end());
+      }
+      f.terms.push_back((uint32_t)(w / mask_words) << GL_TUP_BITS | it->second);
+    }
+    if (!fits) {
+      f.terms.resize(start);
+      break;
+    }
+    f.groups.push_back(NpGroup{(int32_t)start, (int32_t)g.size(), (int32_t)g1});
+  }
+  std::stable_sort(f.groups.begin(), f.groups.end(), [](const NpGroup& a, const NpGroup& b) { return a.len > b.len; });
+  return g1;
+}
+
 void group_mac_np(ckks_ctx* c, int level, int np, const std::vector<std::vector<MacTermNP>>& groups,
                   const std::vector<uint64_t*>& outs, bool accumulate) {
   if (groups.empty()) return;
@@ -1287,9 +1520,6 @@ void group_mac_np(ckks_ctx* c, int level, int np, const std::vector<std::vector<
   }
   for (uint64_t* o : outs)
     if (!o) FICGCN_THROW(EINVAL_, "null output");
-  MacTermNP* td = upload(c, S_GM_TERMS, flat);
-  int* sd = upload(c, S_GM_START, start);
-  uint64_t* const* od = upload(c, S_GM_OUT, outs);
   if (groups.size() > 65535) FICGCN_THROW(EINVAL_, "too many groups in one launch");
   const int n_jb = c->N / (2 * GM_TB), ng = (int)groups.size();
   const bool xcd = n_jb % 8 == 0 && (size_t)n_jb * ng < ((size_t)1 << 31);
@@ -1304,6 +1534,45 @@ void group_mac_np(ckks_ctx* c, int level, int np, const std::vector<std::vector<
   }
   for (size_t gi = 0; gi < groups.size(); ++gi) l25 = l25 && groups[gi].size() <= (size_t)GM_MAX_TERMS;
   const int ar = f50 ? 2 : l25 ? 1 : 0;
+  // The LDS form where it is the faster one: two or three ciphertexts a term and GL_MIN_TERMS terms a
+  // launch.  Measured at N = 2^16, level 2, against the form below (us): 5860 terms over three
+  // ciphertexts 3040 for 4250, 3734 terms 2245 for 2826 (two ciphertexts 1937 for 2149, one 1714 for
+  // 1609), 2062 terms 1787 for 1625 (two 1424 for 1233); with fewer terms its fixed cost, the
+  // ciphertexts' way into LDS, shows, and those of few fit L2 anyway.  Four do not fit its tables.
+  size_t g0 = 0;
+  while (l25 && (np == 2 || np == 3) && flat.size() - start[g0] >= (size_t)GL_MIN_TERMS) {
+    LdsForm f;
+    const size_t g1 = lds_form(c, level, np, groups, g0, f);
+    if (g1 == g0 || f.terms.size() < (size_t)GL_MIN_TERMS) break;
+    const uint64_t* const* tup = upload(c, S_GM_TERMS, f.tuples);
+    const uint32_t* td = upload(c, S_GM_START, f.terms);
+    NpGroup* gd = upload(c, S_GM_GRP, f.groups);
+    uint64_t* const* od = upload(c, S_GM_OUT, outs);
+    ProfScope ps(c, "bsgs_inner");   // the launch alone (its tables are uploaded above)
+    const dim3 lgrid(c->N / GL_COEF, level + 1);
+    const int n_tup = (int)(f.tuples.size() / np), nt = (int)f.terms.size(), nlg = (int)f.groups.size();
+#define GL_LAUNCH(NPV)                                                                                            \
+  hipLaunchKernelGGL(k_group_mac_lds<NPV>, lgrid, dim3(GL_T), 0, c->stream, tup, n_tup, td, nt, gd, nlg, \
+                     f.base, od, level + 1, acc, c->log_n, c->t.mods, c->t.fold25)
+    if (np == 2)
+      GL_LAUNCH(2);
+    else
+      GL_LAUNCH(3);
+#undef GL_LAUNCH
+    HIPCHECK(hipGetLastError());
+    ps.stop();
+    stream_sync(c);
+    g0 = g1;
+  }
+  if (g0) {   // the rest, if any, in the form below
+    if (g0 == groups.size()) return;
+    group_mac_np(c, level, np, std::vector<std::vector<MacTermNP>>(groups.begin() + g0, groups.end()),
+                 std::vector<uint64_t*>(outs.begin() + g0 * np, outs.end()), accumulate);
+    return;
+  }
+  MacTermNP* td = upload(c, S_GM_TERMS, flat);
+  int* sd = upload(c, S_GM_START, start);
+  uint64_t* const* od = upload(c, S_GM_OUT, outs);
   ProfScope ps(c, "bsgs_inner");   // the launch alone (its tables are uploaded above)
 #define GM_LAUNCH(NPV, AV)                                                                                     \
   hipLaunchKernelGGL((k_group_mac_np<NPV, AV>), grid, dim3(GM_TB), 0, c->stream, td, sd, od, level + 1, acc, \
