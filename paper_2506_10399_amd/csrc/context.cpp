@@ -308,7 +308,9 @@ void ensure_device(ckks_ctx* c) {
   std::vector<Fold25> fold(c->n_mod());
   for (int m = 0; m < c->n_mod(); ++m) {
     const uint64_t q = c->mod[m], r25 = (1ull << 25) % q, r50 = (1ull << 50) % q;
-    fold[m] = Fold25{r25, shoup(r25, q), r50, shoup(r50, q), shoup(1, q)};
+    uint64_t P = 1;
+    for (int k = 0; k < c->alpha; ++k) P = (uint64_t)((u128)P * (c->mod[c->L + k] % q) % q);
+    fold[m] = Fold25{r25, shoup(r25, q), r50, shoup(r50, q), shoup(1, q), P};
   }
   HIPCHECK(hipMalloc(&c->t.fold25, fold.size() * sizeof(Fold25)));
   HIPCHECK(hipMemcpy(c->t.fold25, fold.data(), fold.size() * sizeof(Fold25), hipMemcpyHostToDevice));

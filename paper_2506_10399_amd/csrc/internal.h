@@ -41,9 +41,10 @@ FICGCN_FD int lm_mod(const LimbMap& m, int i) {
 inline LimbMap lm_q(int n) { return LimbMap{0, n, 0}; }                     // plain Q limbs 0..n-1
 inline LimbMap lm_ext(int level, int L) { return LimbMap{0, level + 1, L - level - 1}; }  // Q_l then P
 
-// 2^25 and 2^50 modulo a prime, Shoup companions of both and of 1: sums kept in 25-bit halves
+// 2^25 and 2^50 modulo a prime, Shoup companions of both and of 1 (sums kept in 25-bit halves), and
+// the special modulus P modulo the prime
 struct Fold25 {
-  uint64_t r25, r25_s, r50, r50_s, one_s;
+  uint64_t r25, r25_s, r50, r50_s, one_s, P;
 };
 
 // Device-resident per-modulus tables.

@@ -455,6 +455,159 @@ __global__ void k_keymac_masked(const uint64_t* __restrict__ D, const KSJob* __r
   gst(a1, add_mod(v1, reduce128(t1, md), md.q));
 }
 
+// A + B 2^25 + C 2^50 mod q in [0, q) for a prime of the fp64 range.  A word v = v1 2^32 + v0 below 2^63
+// comes back as v1 2^32 (an exact double, its quotient by q below 2^14) brought to (-q, q), plus v0.
+__device__ __forceinline__ uint64_t fold25_fp(uint64_t A, uint64_t B, uint64_t C, double qd, double qinv, const Fold25& f) {
+  auto part = [&](uint64_t v) {
+    return sred((double)(uint32_t)(v >> 32) * 4294967296.0, qd, qinv) + (double)(uint32_t)v;
+  };
+  const double s = part(A) + (fmulmod_s(part(B), (double)f.r25, qd, qinv) + fmulmod_s(part(C), (double)f.r50, qd, qinv));
+  return from_fbits(f2b(canon(sred(s, qd, qinv), qd)));
+}
+// the same for any prime below 2^50, each part lazily to [0, 4q)
+__device__ __forceinline__ uint64_t fold25_int(uint64_t A, uint64_t B, uint64_t C, uint64_t q, const IntQ& iq,
+                                               const Fold25& f) {
+  const uint64_t v = mul_shoup_lazy4(A, 1, f.one_s, iq) + mul_shoup_lazy4(B, f.r25, f.r25_s, iq);
+  return canon8(csub(v, iq.q4, iq.nq4) + mul_shoup_lazy4(C, f.r50, f.r50_s, iq), iq, q);
+}
+constexpr uint32_t M25 = (1u << 25) - 1;
+
+// ---- the same rotations and masks for many outputs ------------------------------------------
+// Where every output takes the same list of (key, Galois element, plaintext) -- the diagonal form of
+// a layer whose packed ciphertexts share their masks -- the plaintexts go into the keys,
+//   A_g[c] = sum_r sum_d D_{src(g,r),d}[sigma_r(j)] (key_{r,d}[c] pt_r)[j],
+// and the rotated first polynomials as well, since ModDown divides by P and P = 0 modulo the special
+// primes: A_g[0] += P sum_r sigma_r(add0_{g,r}) pt_r on the Q limbs gives the words of adding the sum after
+// ModDown.  What is left is one long dot product a coefficient, reduced once.
+//
+// A workgroup holds 64 coefficients of one limb: the list's products in LDS (computed once for all
+// outputs), a lane a coefficient, an output a wave at a time.  sigma maps aligned blocks of 64 indices
+// (bit-reversed order) onto each other, so every read of D is a permuted 512-byte run.
+// Primes below 2^50: words in 25-bit halves, three multiply-adds a product (the sums of x0 k0, x1 k1 and
+// (x0 + x1)(k0 + k1) stay below 2^64 for 4095 terms).  Wider ones: 128-bit sums (ku_rotations).
+// What bounds it: the latency of those reads (18 GB, of which a third hits L2) beside multiply-adds of
+// 1.1 ms at their issue rate.  Waves that share their outputs halve the bytes past L2 but fold more sums:
+// 2.7 ms and more; two outputs a wave read LDS half as often but leave twelve waves: 2.55 ms; sixteen
+// waves of one output, one rotation ahead 2.29 ms, two ahead 2.26 ms (6400-node skeleton layer: 128
+// outputs, 24 rotations, 4 digits, 9 limbs at N = 2^14).  Output by output with 128-bit sums the same
+// products took 3.90 ms, and the first polynomials' part after ModDown 0.73 ms.
+constexpr int KU_T = 1024;
+struct UJob {
+  const uint64_t* key;
+  const uint64_t* pt;
+  uint64_t g;
+};
+struct USrc {
+  const uint64_t* add0;
+  int64_t src;
+};
+constexpr int ku_words(int nd) { return (2 * nd + 1) * 64 + 32; }   // LDS words of one rotation
+
+template <int ND>
+__global__ __launch_bounds__(KU_T) void k_keymac_uniform(const uint64_t* __restrict__ D, const UJob* __restrict__ jobs,
+                                                         const USrc* __restrict__ srcs, int R, int r0, int nr,
+                                                         int n_grp, uint64_t* __restrict__ A, int accumulate, int ext,
+                                                         int l1, int L, int n_mod, int log_n,
+                                                         const Mod* __restrict__ mods,
+                                                         const Fold25* __restrict__ folds) {
+  extern __shared__ uint64_t lds[];
+  uint64_t* const kx = lds;                                    // [nr][2 ND][64] keys times plaintext
+  uint64_t* const px = kx + (size_t)nr * 2 * ND * 64;          // [nr][64] P times plaintext
+  uint32_t* const jx = (uint32_t*)(px + (size_t)nr * 64);      // [nr][64] sigma(j)
+  const size_t N = (size_t)1 << log_n;
+  const int i = blockIdx.y, mi = i < l1 ? i : i - l1 + L;
+  const uint32_t j0 = blockIdx.x * 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const Mod m = cld(mods + mi);
+  const Fold25 f = cld(folds + mi);
+  const bool narrow = m.q < (1ull << 50);
+  auto halves = [](uint64_t x) { return (x & M25) | (x >> 25) << 32; };
+  // a wave prepares one of a rotation's 2 ND + 1 rows at a time
+  for (int u = wave; u < nr * (2 * ND + 1); u += KU_T / 64) {
+    const int r = u / (2 * ND + 1), e = u % (2 * ND + 1);
+    const UJob jb = cld(jobs + r0 + r);
+    const uint64_t p = jb.pt ? gld(jb.pt + (size_t)i * N + j0 + lane) : 1;
+    if (e == 2 * ND) {
+      const uint64_t v = i < l1 ? mul_mod(f.P, p, m) : 0;
+      px[r * 64 + lane] = narrow ? halves(v) : v;
+      jx[r * 64 + lane] = auto_idx(j0 + lane, jb.g, log_n);
+    } else {
+      uint64_t v = gld(jb.key + ((size_t)e * n_mod + mi) * N + j0 + lane);
+      if (jb.pt) v = mul_mod(v, p, m);
+      kx[(r * 2 * ND + e) * 64 + lane] = narrow ? halves(v) : v;
+    }
+  }
+  __syncthreads();
+  const IntQ iq = make_intq(m.q);
+  const bool fp = fp_prime(m.q);
+  const double qd = (double)m.q;
+  const bool q_limb = i < l1;
+  // the words of the next rotations are on their way: two ahead where the registers allow it
+  constexpr int B = ND <= 4 ? 3 : 2;
+  uint64_t x[B][ND], y[B];
+  for (int gi = wave; gi < n_grp; gi += KU_T / 64) {
+    const USrc* ss = srcs + (size_t)gi * R + r0;
+    auto load = [&](uint64_t (&xx)[ND], uint64_t& yy, int r) {
+      const uint32_t jj = jx[r * 64 + lane];
+      const USrc s = cld(ss + r);
+      const uint64_t* d = D + ((size_t)s.src * ND * ext + i) * N;
+#pragma unroll
+      for (int t = 0; t < ND; ++t) xx[t] = d[(size_t)t * ext * N + jj];
+      yy = q_limb ? gld(s.add0 + (size_t)i * N + jj) : 0;
+    };
+    auto walk = [&](auto&& step) {
+#pragma unroll
+      for (int u = 0; u < B - 1; ++u)
+        if (u < nr) load(x[u], y[u], u);
+      for (int r = 0; r < nr; r += B)
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          if (r + u >= nr) break;
+          if (r + u + B - 1 < nr) load(x[(u + B - 1) % B], y[(u + B - 1) % B], r + u + B - 1);
+          step(x[u], y[u], r + u);
+        }
+    };
+    uint64_t* out = A + ((size_t)gi * 2 * ext + i) * N + j0 + lane;
+    auto put = [&](uint64_t v, int c) {
+      uint64_t* o = out + (size_t)c * ext * N;
+      *o = accumulate ? add_mod(v, *o, m.q) : v;
+    };
+    if (narrow) {
+      uint64_t a[2] = {0, 0}, b[2] = {0, 0}, h[2] = {0, 0};
+      auto mac = [&](uint64_t w, uint64_t k, int c) {
+        const uint32_t w0 = (uint32_t)w & M25, w1 = (uint32_t)(w >> 25), k0 = (uint32_t)k, k1 = (uint32_t)(k >> 32);
+        a[c] += (uint64_t)w0 * k0;
+        h[c] += (uint64_t)w1 * k1;
+        b[c] += (uint64_t)(w0 + w1) * (k0 + k1);
+      };
+      walk([&](const uint64_t (&xx)[ND], uint64_t yy, int r) {
+#pragma unroll
+        for (int t = 0; t < ND; ++t)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) mac(xx[t], kx[(r * 2 * ND + 2 * t + c) * 64 + lane], c);
+        mac(yy, px[r * 64 + lane], 0);
+      });
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const uint64_t mid = b[c] - a[c] - h[c];
+        put(fp ? fold25_fp(a[c], mid, h[c], qd, m.qinv, f) : fold25_int(a[c], mid, h[c], m.q, iq, f), c);
+      }
+    } else {
+      u128 s0 = 0, s1 = 0;
+      walk([&](const uint64_t (&xx)[ND], uint64_t yy, int r) {
+#pragma unroll
+        for (int t = 0; t < ND; ++t) {
+          s0 += (u128)xx[t] * kx[(r * 2 * ND + 2 * t) * 64 + lane];
+          s1 += (u128)xx[t] * kx[(r * 2 * ND + 2 * t + 1) * 64 + lane];
+        }
+        if (q_limb) s0 += (u128)yy * px[r * 64 + lane];
+      });
+      put(reduce128(s0, m), 0);
+      put(reduce128(s1, m), 1);
+    }
+  }
+}
+
 // The masked key inner products of a chunk with its jobs taken key by key (runs of jobs
 // sharing one key and Galois element, at most KM_MAXG output groups): a thread per (coefficient,
 // limb) reads each key word once for its run and adds every job's product, times its
@@ -645,6 +798,99 @@ __global__ void k_masked_final(const uint64_t* __restrict__ A, const uint64_t* _
 
 enum { S_KM_A = 80, S_KM_CONV, S_KM_JOBS, S_KM_GRP, S_KM_OUT, S_KM_CGRP, S_KM_RUNS, S_KM_GL, S_KM_P };
 
+// rotations a launch takes: its LDS, and the sums' room (narrow words: 4095 products of 2^52; wide
+// ones: products of two words below 2^bits in 128 bits)
+static int ku_rotations(ckks_ctx* c, int nd) {
+  const int bits = std::max(c->q_bits, c->p_bits);
+  const int wide = 2 * bits >= 128 ? 1 : 1 << std::min(12, 128 - 2 * bits);
+  const int most = std::min((144 << 10) / (ku_words(nd) * 8), std::min(4095, wide - 1) / (nd + 1));
+  return most;
+}
+
+// Every output's list of (key, Galois element, plaintext) is the first one's, and has its add0s
+static bool uniform_jobs(const std::vector<KSJob>& jobs, int n_grp) {
+  if (n_grp < 1 || jobs.empty() || jobs.size() % n_grp) return false;
+  const size_t R = jobs.size() / n_grp;
+  for (size_t k = 0; k < jobs.size(); ++k) {
+    const KSJob &a = jobs[k], &b = jobs[k % R];
+    if (a.grp != (int)(k / R) || a.key != b.key || a.g != b.g || a.pt != b.pt || !a.add0) return false;
+  }
+  return true;
+}
+
+// The masked sums of outputs that share their list: A [n_grp][2][ext][N], first polynomials included
+static void masked_uniform(ckks_ctx* c, int level, const std::vector<const uint64_t*>& sources,
+                           const std::vector<KSJob>& jobs, int n_grp, uint64_t* A) {
+  const size_t N = c->N;
+  const int l1 = level + 1, ext = l1 + c->alpha;
+  const int nd = (l1 + c->alpha - 1) / c->alpha;
+  const int R = (int)(jobs.size() / n_grp);
+  const size_t per_src = (size_t)(nd * ext + l1) * N * 8;
+  std::vector<UJob> list;
+  for (int r = 0; r < R; ++r) list.push_back(UJob{jobs[r].key, jobs[r].pt, jobs[r].g});
+  for (int ga = 0; ga < n_grp;) {
+    // whole outputs, as many as their sources' digits allow
+    std::vector<int> local(sources.size(), -1);
+    std::vector<const uint64_t*> srcs;
+    std::vector<USrc> us;
+    int gb = ga;
+    for (; gb < n_grp; ++gb) {
+      size_t fresh = 0;
+      std::vector<char> seen(sources.size(), 0);
+      for (int r = 0; r < R; ++r) {
+        const int s = jobs[(size_t)gb * R + r].src;
+        if (local[s] < 0 && !seen[s]) ++fresh;
+        seen[s] = 1;
+      }
+      if (gb > ga && (srcs.size() + fresh) * per_src > KS_BUDGET) break;
+      for (int r = 0; r < R; ++r) {
+        const KSJob& jb = jobs[(size_t)gb * R + r];
+        if (local[jb.src] < 0) {
+          local[jb.src] = (int)srcs.size();
+          srcs.push_back(sources[jb.src]);
+        }
+        us.push_back(USrc{jb.add0, local[jb.src]});
+      }
+    }
+    const int U = (int)srcs.size(), ng = gb - ga;
+    const UJob* jd = upload(c, S_KB_JOBS, list);
+    const USrc* ud = upload(c, S_KM_GL, us);
+    const uint64_t* const* sd = upload(c, S_KB_SRC, srcs);
+    uint64_t* tmp = (uint64_t*)dev_scratch(c, S_KB_TMP, (size_t)U * l1 * N * 8);
+    uint64_t* D = (uint64_t*)dev_scratch(c, S_KB_D, (size_t)U * nd * ext * N * 8);
+    {
+      ProfScope pm(c, "modup");
+      modup_batch(c, level, sd, U, tmp, D);
+    }
+    {
+      ProfScope pk(c, "keymac");
+      const int most = ku_rotations(c, nd);
+      for (int r0 = 0; r0 < R; r0 += most) {
+        const int nr = std::min(most, R - r0);
+        uint64_t* Ag = A + (size_t)ga * 2 * ext * N;
+        const size_t bytes = (size_t)nr * ku_words(nd) * 8;
+#define KU_LAUNCH(NDV)                                                                                                \
+  hipLaunchKernelGGL(k_keymac_uniform<NDV>, dim3(N / 64, ext), dim3(KU_T), bytes, c->stream, D, jd, ud, R, r0, nr, ng, \
+                     Ag, r0 ? 1 : 0, ext, l1, c->L, c->n_mod(), c->log_n, c->t.mods, c->t.fold25)
+        switch (nd) {
+          case 1: KU_LAUNCH(1); break;
+          case 2: KU_LAUNCH(2); break;
+          case 3: KU_LAUNCH(3); break;
+          case 4: KU_LAUNCH(4); break;
+          case 5: KU_LAUNCH(5); break;
+          case 6: KU_LAUNCH(6); break;
+          case 7: KU_LAUNCH(7); break;
+          default: KU_LAUNCH(8);
+        }
+#undef KU_LAUNCH
+        HIPCHECK(hipGetLastError());
+      }
+    }
+    stream_sync(c);
+    ga = gb;
+  }
+}
+
 void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64_t*>& sources,
                           const std::vector<KSJob>& jobs, const std::vector<uint64_t*>& outs, bool accumulate) {
   const size_t N = c->N;
@@ -675,6 +921,18 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
   ProfScope ps(c, "ks_masked");
   // one accumulator on the key basis per output, summed over every chunk
   uint64_t* A = (uint64_t*)dev_scratch(c, S_KM_A, (size_t)n_grp * 2 * ext * N * 8);
+  if (fused_basis(c) && !by_key && nd <= KR_MAXD && uniform_jobs(jobs, n_grp)) {
+    masked_uniform(c, level, sources, jobs, n_grp, A);
+    std::vector<FinalJob> finals;
+    for (uint64_t* o : outs) finals.push_back(FinalJob{o, nullptr, nullptr, 1, accumulate ? 1 : 0, 0});
+    const FinalJob* fd = upload(c, S_KM_OUT, finals);
+    uint64_t* conv = (uint64_t*)dev_scratch(c, S_KM_CONV, (size_t)n_grp * 2 * l1 * N * 8);
+    ProfScope pd(c, "moddown");
+    moddown_polys(c, level, A, 2 * n_grp, conv, false);
+    moddown_final(c, level, A, conv, fd, FinalJob{}, n_grp);
+    stream_sync(c);
+    return;
+  }
   zero_fill(c, A, (size_t)n_grp * 2 * ext * N);
   const size_t per_job = 0;   // a job's products go straight into its output's accumulator
   const size_t per_src = (size_t)(nd * ext + l1) * N * 8;
@@ -1136,7 +1394,6 @@ __global__ void __launch_bounds__(GM_TB) k_group_mac_np(const MacTermNP* __restr
 #pragma unroll
       for (int k = 0; k < 4; ++k) res[c][k] = from_fbits(f2b(canon(S[c][k], qd)));
   } else if (AR == 1) {
-    constexpr uint32_t M25 = (1u << 25) - 1;
     uint64_t A[NP][4], B[NP][4], C[NP][4];
 #pragma unroll
     for (int c = 0; c < NP; ++c)
@@ -1300,16 +1557,6 @@ struct NpGroup {
   int32_t start, len, g;   // its terms, its number
 };
 
-// A + B 2^25 + C 2^50 mod q in [0, q) for a prime of the fp64 range.  A word v = v1 2^32 + v0 below 2^63
-// comes back as v1 2^32 (an exact double, its quotient by q below 2^14) brought to (-q, q), plus v0.
-__device__ __forceinline__ uint64_t fold25_fp(uint64_t A, uint64_t B, uint64_t C, double qd, double qinv, const Fold25& f) {
-  auto part = [&](uint64_t v) {
-    return sred((double)(uint32_t)(v >> 32) * 4294967296.0, qd, qinv) + (double)(uint32_t)v;
-  };
-  const double s = part(A) + (fmulmod_s(part(B), (double)f.r25, qd, qinv) + fmulmod_s(part(C), (double)f.r50, qd, qinv));
-  return from_fbits(f2b(canon(sred(s, qd, qinv), qd)));
-}
-
 template <int NP>
 __global__ __launch_bounds__(GL_T) void k_group_mac_lds(
     const uint64_t* const* __restrict__ tuples, int n_tup, const uint32_t* __restrict__ terms, int n_terms,
@@ -1321,7 +1568,6 @@ __global__ __launch_bounds__(GL_T) void k_group_mac_lds(
   typedef __attribute__((address_space(1))) const v2 gv2;
   typedef __attribute__((address_space(1))) v2 gv2w;
   constexpr int T = GL_T;
-  constexpr uint32_t M25 = (1u << 25) - 1;
   constexpr int U = 4;                 // terms a step; masks are two steps ahead
   __shared__ v4 sx[GL_CAP];            // [tuple][NP][2 components][8 lanes]
   __shared__ uint32_t st[GL_LIST];
@@ -1431,13 +1677,8 @@ __global__ __launch_bounds__(GL_T) void k_group_mac_lds(
           for (int w = 0; w < 4; ++w)
             r[w] = fold25_fp(A[c][w], B[c][w] - A[c][w] - C[c][w], C[c][w], qd, m.qinv, f);
         } else {
-          // A + B 2^25 + C 2^50, each part lazily to [0, 4q)
 #pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            const uint64_t v = mul_shoup_lazy4(A[c][w], 1, f.one_s, iq) +
-                               mul_shoup_lazy4(B[c][w] - A[c][w] - C[c][w], f.r25, f.r25_s, iq);
-            r[w] = canon8(csub(v, iq.q4, iq.nq4) + mul_shoup_lazy4(C[c][w], f.r50, f.r50_s, iq), iq, q);
-          }
+          for (int w = 0; w < 4; ++w) r[w] = fold25_int(A[c][w], B[c][w] - A[c][w] - C[c][w], C[c][w], q, iq, f);
         }
 #pragma unroll
         for (int comp = 0; comp < 2; ++comp) {
