@@ -11,8 +11,6 @@
 #include "ks_batch.h"
 
 namespace ficgcn {
-void decode_values(int N, const std::vector<double>& m, double scale, double* re, double* im, size_t n);
-void crt_center(const std::vector<uint64_t>& mods, const uint64_t* res, int N, std::vector<double>& out);
 
 static thread_local std::string g_err;
 void set_error(const std::string& m) { g_err = m; }
@@ -368,13 +366,7 @@ ficgcn_status ckks_decrypt(ckks_ctx* ctx, const ckks_keys* client_keys, const ui
     uint64_t* m = (uint64_t*)ctx->buf(13, (size_t)l1 * N * 8);
     decrypt_core(ctx, ct_dev, client_keys->s_ntt, level, m);
     ntt_inv(ctx, m, l1, lm_q(l1), 1, 0);
-    std::vector<uint64_t> host((size_t)l1 * N);
-    HIPCHECK(hipMemcpyAsync(host.data(), m, host.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHECK(hipStreamSynchronize(ctx->stream));
-    std::vector<uint64_t> mods(ctx->mod.begin(), ctx->mod.begin() + l1);
-    std::vector<double> coef;
-    crt_center(mods, host.data(), (int)N, coef);
-    decode_values((int)N, coef, scale, re, im, n_slots);
+    decode_gpu(ctx, m, l1, scale, re, im, std::min(n_slots, N / 2));
   });
 }
 

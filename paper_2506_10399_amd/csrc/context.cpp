@@ -459,6 +459,8 @@ ckks_ctx::~ckks_ctx() {
     if (p) (void)hipFree(p);
   if (enc_pos) (void)hipFree(enc_pos);
   if (enc_flag) (void)hipFree(enc_flag);
+  if (dec_inv) (void)hipFree(dec_inv);
+  if (dec_host) (void)hipHostFree(dec_host);
   if (t.mods) (void)hipFree(t.mods);
   if (t.fold25) (void)hipFree(t.fold25);
   if (mid_src) (void)hipFree(mid_src);

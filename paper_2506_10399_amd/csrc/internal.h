@@ -153,6 +153,10 @@ struct ckks_ctx {
   double* enc_twist = nullptr;   // [N] (re, im)
   uint32_t* enc_pos = nullptr;   // [N] slot j -> FFT input of the slot and of its conjugate
   int* enc_flag = nullptr;       // set when a coefficient leaves 63 bits
+  // of the decoder: q_j^-1 mod q_i and its Shoup quotient at (i L + j) for j < i, [L][L][2]; decoded slots
+  // (re, then im) in host memory
+  uint64_t* dec_inv = nullptr;
+  double* dec_host = nullptr;    // [2][N/2]
   // kernel timing (HIP events on `stream`), see ficgcn_profile_enable
   bool profiling = false;
   std::map<std::string, std::vector<std::pair<hipEvent_t, hipEvent_t>>> prof;
@@ -255,7 +259,7 @@ void mac_ext(ckks_ctx* c, uint64_t* A, const uint64_t* acc, const uint64_t* pt, 
 void encode_batch_ext(ckks_ctx* c, const double* re, size_t count, size_t n, double scale, int level, uint64_t* dev);
 void pt_load_ext(ckks_ctx* c, const uint64_t* host, int level, uint64_t* dev);
 
-// ---- encoding (encode.cpp on the host, encode_gpu.hip on the device) ----
+// ---- encoding and decoding (tables in encode.cpp, kernels in encode_gpu.hip) ----
 // host tables of the canonical-embedding encoder: root[k] = exp(-2 pi i k / N)
 // (k < N/2) and twist[i] = exp(-i pi i / N) (i < N) as (re, im) pairs; pos[2j],
 // pos[2j+1] = the FFT inputs of slot j and of its conjugate
@@ -266,6 +270,9 @@ void encode_tables(int N, std::vector<double>& root, std::vector<double>& twist,
 // 63 bits.
 void encode_gpu(ckks_ctx* c, const double* re, const double* im, size_t count, size_t n, double scale, int n_limbs,
                 LimbMap map, uint64_t* dev);
+// slots [0, n) (n <= N/2) of the polynomial whose residues over q_0..q_{k-1} m holds in coefficient form
+// (overwritten), centred and divided by scale; re or im may be null.  Waits for the stream.
+void decode_gpu(ckks_ctx* c, uint64_t* m, int k, double scale, double* re, double* im, size_t n);
 
 // ---- sampling (sample.hip) ----
 void sample_uniform(ckks_ctx* c, uint64_t* out, uint64_t seed, uint32_t kind, uint32_t a, uint32_t b0,
