@@ -458,6 +458,7 @@ ckks_ctx::~ckks_ctx() {
   for (double* p : {t.psi_f, t.ipsi_f, enc_root, enc_twist})
     if (p) (void)hipFree(p);
   if (enc_pos) (void)hipFree(enc_pos);
+  if (enc_src) (void)hipFree(enc_src);
   if (enc_flag) (void)hipFree(enc_flag);
   if (dec_inv) (void)hipFree(dec_inv);
   if (dec_host) (void)hipHostFree(dec_host);

@@ -51,7 +51,8 @@ static const std::vector<uint32_t>& slot_exponents(int N) {
   return cache[N] = r;
 }
 
-void encode_tables(int N, std::vector<double>& root, std::vector<double>& twist, std::vector<uint32_t>& pos) {
+void encode_tables(int N, std::vector<double>& root, std::vector<double>& twist, std::vector<uint32_t>& pos,
+                   std::vector<uint32_t>& src) {
   const FftTables& T = tables(N);
   const std::vector<uint32_t>& r = slot_exponents(N);
   root.resize((size_t)N);
@@ -64,10 +65,12 @@ void encode_tables(int N, std::vector<double>& root, std::vector<double>& twist,
     twist[2 * i] = T.twist[i].real();
     twist[2 * i + 1] = T.twist[i].imag();
   }
-  pos.resize((size_t)N);
+  pos.resize((size_t)N / 2);
+  src.resize((size_t)N);
   for (int j = 0; j < N / 2; ++j) {
-    pos[2 * j] = (r[j] - 1) / 2;
-    pos[2 * j + 1] = ((2 * (uint32_t)N - r[j]) - 1) / 2;
+    pos[j] = (r[j] - 1) / 4;
+    src[(r[j] - 1) / 2] = 2 * (uint32_t)j;
+    src[(2 * (uint32_t)N - r[j] - 1) / 2] = 2 * (uint32_t)j + 1;
   }
 }
 

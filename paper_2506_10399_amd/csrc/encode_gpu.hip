@@ -9,8 +9,10 @@
 //   row pass   : for each i1 < N1, the N2-point DFT over s2 of that row, written
 //                in natural order, FFT(v)_{i1 + N1 i2}.
 // Each sub-DFT is an in-LDS radix-2 transform (bit-reversed load) of a block of
-// COLS columns or rows.  Then one kernel rounds, checks the 63-bit range and
-// writes the residues of every limb, and the NTT takes them to evaluation form.
+// COLS columns or rows.  The column pass gathers its input from the slot values, the
+// row pass rounds and checks the 63-bit range, and the NTT's column pass takes every
+// limb's residues from the rounded coefficients.  (24 plaintexts of 7 limbs at N = 2^16: 110 us
+// on the device, with passes of their own to scatter, round and write residues 196 us.)
 // Independent fp64 FFTs can round a coefficient differently when its scaled
 // value sits within the FFT's error of a half-integer; decoding absorbs it.
 //
@@ -22,7 +24,7 @@
 // 2.9 ms of 2.97 ms.  The root mean square error against extended precision is 0.89 to 0.94 times that
 // transform's (N = 2^12 to 2^16).
 #include "internal.h"
-#include "ks_common.h"
+#include "ntt_dev.h"
 
 namespace ficgcn {
 
@@ -39,18 +41,39 @@ __device__ __forceinline__ cplx csub(cplx a, cplx b) { return make_double2(a.x -
 constexpr int ET = 256;           // threads per block
 constexpr int ENC_LDS = 32768;    // bytes of LDS per block: COLS * C complex values
 
-// v[b][pos[2j]] = z_j, v[b][pos[2j+1]] = conj(z_j), z_j = (re, im) (zero past n)
-__global__ void k_enc_scatter(const double* __restrict__ re, const double* __restrict__ im, size_t n,
-                              const uint32_t* __restrict__ pos, cplx* __restrict__ v, int N) {
-  const size_t j = blockIdx.x * (size_t)ET + threadIdx.x;
-  const size_t b = blockIdx.y;
-  if (j >= (size_t)N / 2) return;
-  const double x = j < n ? re[b * n + j] : 0.0;
-  const double y = j < n && im ? im[b * n + j] : 0.0;
-  cplx* vb = v + b * (size_t)N;
-  vb[pos[2 * j]] = make_double2(x, y);
-  vb[pos[2 * j + 1]] = make_double2(x, -y);
-}
+// The transform's input and output.  Encoding: input g is the value of slot src[g] >> 1 (zero past n), its
+// conjugate when src[g] is odd; output i gives the coefficient m_i, rounded half to even.
+struct EncodeIo {
+  const double *re, *im;
+  size_t n;
+  const uint32_t* src;
+  const cplx* twist;
+  double scale;
+  int64_t* m;
+  int* flag;
+  __device__ __forceinline__ cplx in(const cplx*, size_t b, size_t g, int) const {
+    const uint32_t u = src[g], j = u >> 1;
+    const double x = j < n ? re[b * n + j] : 0.0;
+    const double y = j < n && im ? im[b * n + j] : 0.0;
+    return make_double2(x, u & 1 ? -y : y);
+  }
+  __device__ __forceinline__ void out(cplx*, size_t b, size_t i, int N, cplx x) const {
+    const cplx t = twist[i];
+    const double v = (t.x * x.x - t.y * x.y) / (double)N * scale;
+    int64_t r = 0;
+    if (fabs(v) < 9.2e18)
+      r = (int64_t)rint(v);
+    else
+      *flag = 1;
+    m[b * N + i] = r;
+  }
+};
+// Decoding: complex values from and to memory
+struct DecodeIo {
+  cplx* V;
+  __device__ __forceinline__ cplx in(const cplx* v, size_t b, size_t g, int N) const { return v[b * N + g]; }
+  __device__ __forceinline__ void out(cplx*, size_t b, size_t i, int N, cplx x) const { V[b * N + i] = x; }
+};
 
 __device__ __forceinline__ uint32_t brev_bits(uint32_t x, int bits) { return __brev(x) >> (32 - bits); }
 
@@ -66,9 +89,8 @@ __device__ __forceinline__ cplx wpow(const cplx* __restrict__ root, uint32_t e, 
 // unit u = column s2, element s1 at N2 s1 + s2, result times w^(s2 i1) back in
 // place.  Row pass: unit u = row i1, element s2 at N2 i1 + s2, result i2 to
 // out[i1 + N1 i2].  RS: N is the ring degree (1, encoding) or its half (2, decoding), in the ring's table.
-template <bool ROW, int RS>
-__global__ __launch_bounds__(ET) void k_enc_fft(cplx* __restrict__ v, cplx* __restrict__ out,
-                                                const cplx* __restrict__ root, int N, int N1, int N2, int logC,
+template <bool ROW, int RS, class Io>
+__global__ __launch_bounds__(ET) void k_enc_fft(cplx* __restrict__ v, Io io, const cplx* __restrict__ root, int N, int N1, int N2, int logC,
                                                 int COLS) {
   extern __shared__ cplx sh[];
   const int C = 1 << logC;
@@ -89,7 +111,7 @@ __global__ __launch_bounds__(ET) void k_enc_fft(cplx* __restrict__ v, cplx* __re
       e = t / COLS;
       g = (size_t)N2 * e + u0 + col;
     }
-    sh[col * C + brev_bits((uint32_t)e, logC)] = vb[g];
+    sh[col * C + brev_bits((uint32_t)e, logC)] = ROW ? vb[g] : io.in(v, b, g, N);
   }
   __syncthreads();
   // radix-2 stages, twiddles w_C^k = w^(k N / C)
@@ -114,7 +136,7 @@ __global__ __launch_bounds__(ET) void k_enc_fft(cplx* __restrict__ v, cplx* __re
   for (int t = threadIdx.x; t < total; t += ET) {
     if (ROW) {
       const int col = t % COLS, i2 = t / COLS;   // consecutive threads: consecutive rows i1
-      out[b * (size_t)N + (size_t)(u0 + col) + (size_t)N1 * i2] = sh[col * C + i2];
+      io.out(v, b, (size_t)(u0 + col) + (size_t)N1 * i2, N, sh[col * C + i2]);
     } else {
       const int col = t % COLS, i1 = t / COLS;
       const uint32_t e = (uint32_t)(((uint64_t)(u0 + col) * (uint64_t)i1) % (uint64_t)N);
@@ -124,45 +146,51 @@ __global__ __launch_bounds__(ET) void k_enc_fft(cplx* __restrict__ v, cplx* __re
   }
 }
 
-// m_i = Re(twist_i * V_i) / N * scale, rounded half to even; residues of every limb
-__global__ void k_enc_final(const cplx* __restrict__ V, const cplx* __restrict__ twist, double scale, int N,
-                            LimbMap map, int n_limbs, const Mod* __restrict__ mods, uint64_t* __restrict__ pt,
-                            int* __restrict__ flag) {
-  const size_t i = blockIdx.x * (size_t)ET + threadIdx.x;
-  const size_t b = blockIdx.y;
-  if (i >= (size_t)N) return;
-  const cplx x = V[b * (size_t)N + i], t = twist[i];
-  const double m = (t.x * x.x - t.y * x.y) / (double)N * scale;
-  int64_t r = 0;
-  if (fabs(m) < 9.2e18)
-    r = (int64_t)rint(m);
-  else
-    *flag = 1;
-  uint64_t* out = pt + b * (size_t)n_limbs * N;
-  for (int l = 0; l < n_limbs; ++l) {
-    const Mod md = mods[lm_mod(map, l)];
-    const uint64_t a = r >= 0 ? reduce128((u128)(uint64_t)r, md) : md.q - 1 - reduce128((u128)(uint64_t)(-(r + 1)), md);
-    out[(size_t)l * N + i] = a;
+// The transform's column pass reads the rounded coefficients, so the residues are never written in coefficient
+// form: |r| < 2^63 as (its high half 2^32 reduced) + its low half, or Shoup's product with 1, in [0, 4q), and
+// its negative
+struct CoefSrc {
+  const int64_t* m;
+  const Fold25* folds;
+  template <int LOGC, bool FP>
+  __device__ __forceinline__ void load(uint64_t (&x)[8], uint64_t*, const MidPlace<LOGC>& p, int mi, const Mod&, int z,
+                                       const Tw& t, int log_n) const {
+    const int64_t* a = m + ((size_t)z << log_n) + p.unit;
+    const uint64_t one_s = FP ? 0 : cld(&folds[mi].one_s);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = (uint64_t)a[(size_t)(p.r + MidGeo<LOGC>::TPC * u) << (log_n - LOGC)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t r = (int64_t)x[u];
+      if (FP) {
+        x[u] = f2b(sred((double)(int32_t)(r >> 32) * 4294967296.0, t.qd, t.qinv) + (double)(uint32_t)r);
+      } else {
+        const uint64_t v = mul_shoup_lazy4((uint64_t)(r < 0 ? -r : r), 1, one_s, t.c);
+        x[u] = r < 0 ? t.c.q4 - v : v;
+      }
+    }
   }
-}
+};
 
 static void ensure_enc_tables(ckks_ctx* c) {
   if (c->enc_root) return;
   std::vector<double> root, twist;
-  std::vector<uint32_t> pos;
-  encode_tables(c->N, root, twist, pos);
+  std::vector<uint32_t> pos, src;
+  encode_tables(c->N, root, twist, pos, src);
   HIPCHECK(hipMalloc(&c->enc_root, root.size() * 8));
   HIPCHECK(hipMemcpy(c->enc_root, root.data(), root.size() * 8, hipMemcpyHostToDevice));
   HIPCHECK(hipMalloc(&c->enc_twist, twist.size() * 8));
   HIPCHECK(hipMemcpy(c->enc_twist, twist.data(), twist.size() * 8, hipMemcpyHostToDevice));
   HIPCHECK(hipMalloc(&c->enc_pos, pos.size() * 4));
   HIPCHECK(hipMemcpy(c->enc_pos, pos.data(), pos.size() * 4, hipMemcpyHostToDevice));
+  HIPCHECK(hipMalloc(&c->enc_src, src.size() * 4));
+  HIPCHECK(hipMemcpy(c->enc_src, src.data(), src.size() * 4, hipMemcpyHostToDevice));
   HIPCHECK(hipMalloc(&c->enc_flag, sizeof(int)));
 }
 
-// the two passes over n_pt transforms of N points from v to V
-template <int RS>
-static void launch_fft(ckks_ctx* c, cplx* v, cplx* V, int n_pt, int N) {
+// the two passes over n_pt transforms of N points through v
+template <int RS, class Io>
+static void launch_fft(ckks_ctx* c, cplx* v, const Io& io, int n_pt, int N) {
   int l1 = 0;
   while ((1 << (2 * (l1 + 1))) <= N) ++l1;   // N1 = 2^floor(log N / 2)
   const int N1 = 1 << l1, N2 = N / N1;
@@ -174,8 +202,8 @@ static void launch_fft(ckks_ctx* c, cplx* v, cplx* V, int n_pt, int N) {
     int cols = std::min(ENC_LDS / (int)(C * sizeof(cplx)), units);
     while (cols > 4 && (int64_t)units / cols * n_pt < 256) cols /= 2;
     if (cols < 1 || units % cols) FICGCN_THROW(EINVAL_, "embedding FFT shape");
-    hipLaunchKernelGGL(row ? (k_enc_fft<true, RS>) : (k_enc_fft<false, RS>), dim3(units / cols, n_pt), dim3(ET),
-                       (size_t)cols * C * sizeof(cplx), c->stream, v, V, (const cplx*)c->enc_root, N, N1, N2, logC,
+    hipLaunchKernelGGL(row ? (k_enc_fft<true, RS, Io>) : (k_enc_fft<false, RS, Io>), dim3(units / cols, n_pt), dim3(ET),
+                       (size_t)cols * C * sizeof(cplx), c->stream, v, io, (const cplx*)c->enc_root, N, N1, N2, logC,
                        cols);
     HIPCHECK(hipGetLastError());
   }
@@ -188,13 +216,13 @@ void encode_gpu(ckks_ctx* c, const double* re, const double* im, size_t count, s
   if (!re && n > 0) FICGCN_THROW(EINVAL_, "null slot values");
   ensure_enc_tables(c);
   const int N = c->N;
-  // chunks of plaintexts: slot values, the FFT buffer and its natural-order output
+  // chunks of plaintexts: slot values, the FFT buffer and the coefficients
   const size_t CH = 32;
   const size_t nn = n > 0 ? n : 1;
   double* d_re = (double*)dev_scratch(c, 17, CH * nn * 8 * (im ? 2 : 1));
   double* d_im = im ? d_re + CH * nn : nullptr;
   cplx* v = (cplx*)dev_scratch(c, 18, CH * (size_t)N * sizeof(cplx));
-  cplx* V = (cplx*)dev_scratch(c, 19, CH * (size_t)N * sizeof(cplx));
+  int64_t* m = (int64_t*)dev_scratch(c, 19, CH * (size_t)N * 8);
   HIPCHECK(hipMemsetAsync(c->enc_flag, 0, sizeof(int), c->stream));
   for (size_t b0 = 0; b0 < count; b0 += CH) {
     const int nb = (int)std::min(CH, count - b0);
@@ -202,15 +230,11 @@ void encode_gpu(ckks_ctx* c, const double* re, const double* im, size_t count, s
       HIPCHECK(hipMemcpyAsync(d_re, re + b0 * n, (size_t)nb * n * 8, hipMemcpyHostToDevice, c->stream));
       if (im) HIPCHECK(hipMemcpyAsync(d_im, im + b0 * n, (size_t)nb * n * 8, hipMemcpyHostToDevice, c->stream));
     }
-    hipLaunchKernelGGL(k_enc_scatter, dim3((N / 2 + ET - 1) / ET, nb), dim3(ET), 0, c->stream, d_re, d_im, n,
-                       c->enc_pos, v, N);
-    HIPCHECK(hipGetLastError());
-    launch_fft<1>(c, v, V, nb, N);
+    launch_fft<1>(c, v, EncodeIo{d_re, d_im, n, c->enc_src, (const cplx*)c->enc_twist, scale, m, c->enc_flag}, nb, N);
     uint64_t* pt = dev + b0 * (size_t)n_limbs * N;
-    hipLaunchKernelGGL(k_enc_final, dim3((N + ET - 1) / ET, nb), dim3(ET), 0, c->stream, V, (const cplx*)c->enc_twist,
-                       scale, N, map, n_limbs, c->t.mods, pt, c->enc_flag);
-    HIPCHECK(hipGetLastError());
-    ntt_fwd(c, pt, n_limbs, map, nb, (size_t)n_limbs * N);
+    const size_t stride = (size_t)n_limbs * N;
+    src_cols(c, pt, stride, CoefSrc{m, c->t.fold25}, n_limbs, map, nb);
+    ntt_fwd_rows(c, pt, n_limbs, map, nb, stride);
     // the host slot values of this chunk are re-read by the next chunk's copy only after this point
     HIPCHECK(hipStreamSynchronize(c->stream));
   }
@@ -283,12 +307,12 @@ __global__ __launch_bounds__(ET) void k_dec_lift(uint64_t* __restrict__ m, int N
   if (h == 0 && i < (size_t)N / 2) v[i] = cmul_fma(make_double2(x[u], -x[u + ET / 2]), twist[i]);
 }
 
-// slot j is the conjugate of V_t, 4 t + 1 = 5^j; pos[2j] = 2 t.  The results go straight to host memory.
+// slot j is the conjugate of V_t, t = pos[j], 4 t + 1 = 5^j.  The results go straight to host memory.
 __global__ void k_dec_gather(const cplx* __restrict__ V, const uint32_t* __restrict__ pos, size_t n,
                              double* __restrict__ re, double* __restrict__ im) {
   const size_t j = blockIdx.x * (size_t)ET + threadIdx.x;
   if (j >= n) return;
-  const cplx x = V[pos[2 * j] / 2];
+  const cplx x = V[pos[j]];
   re[j] = x.x;
   im[j] = -x.y;
 }
@@ -319,7 +343,7 @@ void decode_gpu(ckks_ctx* c, uint64_t* m, int k, double scale, double* re, doubl
     hipLaunchKernelGGL(k_dec_lift, dim3((H + ET / 2 - 1) / (ET / 2)), dim3(ET), 0, c->stream, m, (int)N, k, scale,
                        c->dec_inv, c->L, c->t.mods, (const cplx*)c->enc_twist, v);
     HIPCHECK(hipGetLastError());
-    launch_fft<2>(c, v, V, 1, (int)H);
+    launch_fft<2>(c, v, DecodeIo{V}, 1, (int)H);
     hipLaunchKernelGGL(k_dec_gather, dim3((n + ET - 1) / ET), dim3(ET), 0, c->stream, V, c->enc_pos, n, c->dec_host,
                        c->dec_host + H);
     HIPCHECK(hipGetLastError());

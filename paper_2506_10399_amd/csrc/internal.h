@@ -151,7 +151,8 @@ struct ckks_ctx {
   // device tables of the GPU encoder (built on its first use)
   double* enc_root = nullptr;    // [N/2] (re, im)
   double* enc_twist = nullptr;   // [N] (re, im)
-  uint32_t* enc_pos = nullptr;   // [N] slot j -> FFT input of the slot and of its conjugate
+  uint32_t* enc_src = nullptr;   // [N] input of the encoder's transform -> 2 slot, + 1 for the conjugate
+  uint32_t* enc_pos = nullptr;   // [N/2] slot -> output of the decoder's transform
   int* enc_flag = nullptr;       // set when a coefficient leaves 63 bits
   // of the decoder: q_j^-1 mod q_i and its Shoup quotient at (i L + j) for j < i, [L][L][2]; decoded slots
   // (re, then im) in host memory
@@ -261,9 +262,10 @@ void pt_load_ext(ckks_ctx* c, const uint64_t* host, int level, uint64_t* dev);
 
 // ---- encoding and decoding (tables in encode.cpp, kernels in encode_gpu.hip) ----
 // host tables of the canonical-embedding encoder: root[k] = exp(-2 pi i k / N)
-// (k < N/2) and twist[i] = exp(-i pi i / N) (i < N) as (re, im) pairs; pos[2j],
-// pos[2j+1] = the FFT inputs of slot j and of its conjugate
-void encode_tables(int N, std::vector<double>& root, std::vector<double>& twist, std::vector<uint32_t>& pos);
+// (k < N/2) and twist[i] = exp(-i pi i / N) (i < N) as (re, im) pairs; src[g] = 2 j (2 j + 1) where the
+// encoder's transform takes slot j (its conjugate) as input g; pos[j] = the decoder's output of slot j
+void encode_tables(int N, std::vector<double>& root, std::vector<double>& twist, std::vector<uint32_t>& pos,
+                   std::vector<uint32_t>& src);
 // count plaintexts of the slot values re (and im, may be null) [count][n], at
 // `scale`, as residues over n_limbs limbs (modulus lm_mod(map, i)) in
 // evaluation form: dev [count][n_limbs][N].  ESCALE if a coefficient leaves

@@ -25,12 +25,6 @@
 namespace ficgcn {
 
 // ---- inverse row pass, out of place --------------------------------------------------------
-// One wave per workgroup: RC chunks of C words, so a barrier costs nothing.
-template <int LOGC>
-constexpr int row_cols() {
-  return 64 / PassGeo<LOGC, 1>::TPC;
-}
-
 struct ModUpSrc {
   const uint64_t* const* srcs;   // or null: `one`
   const uint64_t* one;
@@ -117,169 +111,7 @@ __global__ __launch_bounds__(64) void k_inv_rows(S src, int log_n, const uint64_
 // entries of tables made with the context: a block's next entry arrives by a scalar load while the
 // transform before it runs.
 //
-// A block of 16 columns (128-byte runs of a limb's rows) has TPC = C / 8 threads a column with 8
-// elements each, so that both sources' coefficients and a destination's fit 128 registers and four
-// waves a SIMD hide each other's waits (with 16 elements a thread, two waves a SIMD, the ModUp above
-// took 105 us).  The stages run in up to three layouts of a thread's elements:
-//   A  r + TPC u                              the three widest butterflies;
-//   B  (r / S) 8 S + r % S + S u, S = TPC / 8 the next three (TPC > 8; else B is C);
-//   C  8 r + v                                the rest.
-// A to B goes through LDS with one barrier; B to C stays within a wave (the S threads of a group
-// times 16 columns are at most 64 lanes).  LDS is double buffered: the next transform's stores
-// cannot meet the previous one's loads, which every wave has done before the barrier between.
-constexpr int MID_COLS = 16;
-template <int LOGC>
-struct MidGeo {
-  static constexpr int C = 1 << LOGC;
-  static constexpr int EPT = 8;
-  static constexpr int TPC = C / 8;
-  static constexpr int S = TPC > 8 ? TPC / 8 : 1;
-  static constexpr int THREADS = TPC * MID_COLS;
-  static constexpr int BUF = MID_COLS * (C + C / 8);   // a pad row per eight spreads layout C over the banks
-};
-// LDS word of element e: (e + e / 8) 16 + column.  In every layout that is a base of the thread plus
-// a constant of u (a layout's steps never carry the first element's remainder past a row of eight).
-template <int LOGC>
-struct MidPlace {
-  typedef MidGeo<LOGC> G;
-  int r, unit, e0b, sa, sb, sc;
-  __device__ __forceinline__ MidPlace(int tid, int block)
-      : r(tid / MID_COLS), unit(block * MID_COLS + tid % MID_COLS), e0b((r / G::S) * (8 * G::S) + r % G::S) {
-    const int col = tid % MID_COLS;
-    sa = (r + (r >> 3)) * MID_COLS + col;
-    sb = (e0b + (r / G::S) * G::S) * MID_COLS + col;
-    sc = 9 * r * MID_COLS + col;
-  }
-  __device__ __forceinline__ int a(int u) const { return sa + (G::TPC * u + ((G::TPC * u) >> 3)) * MID_COLS; }
-  __device__ __forceinline__ int b(int u) const { return sb + (G::S * u + ((G::S * u) >> 3)) * MID_COLS; }
-  __device__ __forceinline__ int c(int v) const { return sc + v * MID_COLS; }
-  // word of element 8 r + v of a limb: v's part is the same for every thread
-  __device__ __forceinline__ uint32_t word(int log_n) const { return ((uint32_t)(8 * r) << (log_n - LOGC)) + unit; }
-  __device__ __forceinline__ size_t row(int v, int log_n) const { return (size_t)v << (log_n - LOGC); }
-};
-// twiddles of stages [S0, S1) on a thread's 8 elements, whose first is e0 and whose step is STEP;
-// stage st pairs elements C >> (st + 1) apart
-template <bool FP>
-struct MidTw {
-  uint64_t w[7], ws[FP ? 1 : 7];
-};
-template <int LOGC, bool FP, int S0, int S1, int STEP, bool UNIFORM>
-__device__ __forceinline__ void mid_tw(MidTw<FP>& m, int e0, const Tw& t) {
-  int n = 0;
-#pragma unroll
-  for (int st = S0; st < S1; ++st) {
-    const int d = (1 << LOGC) >> (st + 1);
-    const int ng = 4 / (d / STEP) > 0 ? 4 / (d / STEP) : 1;
-#pragma unroll
-    for (int g = 0; g < ng; ++g) {
-      const int k = (1 << st) + e0 / (2 * d) + g;
-      if (UNIFORM) {
-        m.w[n] = FP ? f2b(cld(t.Wf + k)) : cld(t.W + k);
-        if (!FP) m.ws[n] = cld(t.Ws + k);
-      } else {
-        m.w[n] = FP ? f2b(t.Wf[k]) : t.W[k];
-        if (!FP) m.ws[n] = t.Ws[k];
-      }
-      ++n;
-    }
-  }
-}
-template <int LOGC, bool FP, bool INV, int S0, int S1, int STEP>
-__device__ __forceinline__ void mid_stages(uint64_t (&x)[8], const MidTw<FP>& m, const Tw& t) {
-#pragma unroll
-  for (int i = S0; i < S1; ++i) {
-    const int st = INV ? S1 - 1 - (i - S0) : i;
-    const int du = ((1 << LOGC) >> (st + 1)) / STEP;   // the pair's distance in this thread's elements
-    int n = 0;
-    for (int s = S0; s < st; ++s) n += 4 / (((1 << LOGC) >> (s + 1)) / STEP) > 0 ? 4 / (((1 << LOGC) >> (s + 1)) / STEP) : 1;
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if ((u & du) == 0) {
-        const int g = n + u / (2 * du);
-        if (INV)
-          bfly_inv<FP>(x[u], x[u + du], m.w[g], FP ? 0 : m.ws[FP ? 0 : g], t.c, t.qd, t.qinv, red_inv(st, LOGC));
-        else
-          bfly_fwd<FP>(x[u], x[u + du], m.w[g], FP ? 0 : m.ws[FP ? 0 : g], t.c, t.qd, t.qinv, red_fwd(st, LOGC));
-      }
-  }
-}
-// the wave's own LDS words, stored by one lane and loaded by another: in program order
-__device__ __forceinline__ void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-// layout A -> layout C, forward stages; s: this transform's LDS buffer.  In fp64 each layout's
-// twiddles are requested before the wait of the layout before it, `first` (layout B's, or C's when
-// there is no B) before the map; the integer form's, twice as many registers, where they are used.
-template <int LOGC, bool FP>
-__device__ __forceinline__ void mid_fwd_first(MidTw<FP>& m, const MidPlace<LOGC>& p, const Tw& t) {
-  typedef MidGeo<LOGC> G;
-  if (G::S > 1)
-    mid_tw<LOGC, FP, 3, (G::S > 1 ? 6 : 3), G::S, false>(m, p.e0b, t);
-  else
-    mid_tw<LOGC, FP, 3, (G::S > 1 ? 3 : LOGC), 1, false>(m, 8 * p.r, t);
-}
-template <int LOGC, bool FP>
-__device__ __forceinline__ void mid_fwd(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC>& p, const Tw& t,
-                                        MidTw<FP>& first) {
-  typedef MidGeo<LOGC> G;
-  {
-    MidTw<FP> a;
-    mid_tw<LOGC, FP, 0, 3, G::TPC, true>(a, 0, t);
-    mid_stages<LOGC, FP, false, 0, 3, G::TPC>(x, a, t);
-  }
-#pragma unroll
-  for (int u = 0; u < 8; ++u) s[p.a(u)] = x[u];
-  __syncthreads();
-  if (!FP) mid_fwd_first<LOGC, FP>(first, p, t);
-  if (G::S > 1) {
-    MidTw<FP> c;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) x[u] = s[p.b(u)];
-    if (FP) mid_tw<LOGC, FP, 6, (G::S > 1 ? LOGC : 6), 1, false>(c, 8 * p.r, t);
-    mid_stages<LOGC, FP, false, 3, (G::S > 1 ? 6 : 3), G::S>(x, first, t);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s[p.b(u)] = x[u];
-    wave_order();
-#pragma unroll
-    for (int v = 0; v < 8; ++v) x[v] = s[p.c(v)];
-    if (!FP) mid_tw<LOGC, FP, 6, (G::S > 1 ? LOGC : 6), 1, false>(c, 8 * p.r, t);
-    mid_stages<LOGC, FP, false, 6, (G::S > 1 ? LOGC : 6), 1>(x, c, t);
-  } else {
-#pragma unroll
-    for (int v = 0; v < 8; ++v) x[v] = s[p.c(v)];
-    mid_stages<LOGC, FP, false, 3, (G::S > 1 ? 3 : LOGC), 1>(x, first, t);
-  }
-}
-// layout C -> layout A, inverse stages
-template <int LOGC, bool FP>
-__device__ __forceinline__ void mid_inv(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC>& p, const Tw& t) {
-  typedef MidGeo<LOGC> G;
-  constexpr int SC = G::S > 1 ? 6 : 3;   // first stage of layout C
-  MidTw<FP> c, b;
-  mid_tw<LOGC, FP, SC, LOGC, 1, false>(c, 8 * p.r, t);
-  if (FP && G::S > 1) mid_tw<LOGC, FP, 3, SC, G::S, false>(b, p.e0b, t);
-  mid_stages<LOGC, FP, true, SC, LOGC, 1>(x, c, t);
-#pragma unroll
-  for (int v = 0; v < 8; ++v) s[p.c(v)] = x[v];
-  if (G::S > 1) {
-    wave_order();
-#pragma unroll
-    for (int u = 0; u < 8; ++u) x[u] = s[p.b(u)];
-    if (!FP) mid_tw<LOGC, FP, 3, SC, G::S, false>(b, p.e0b, t);
-    mid_stages<LOGC, FP, true, 3, SC, G::S>(x, b, t);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s[p.b(u)] = x[u];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < 8; ++u) x[u] = s[p.a(u)];
-  MidTw<FP> a;
-  mid_tw<LOGC, FP, 0, 3, G::TPC, true>(a, 0, t);
-  mid_stages<LOGC, FP, true, 0, 3, G::TPC>(x, a, t);
-}
-
+// The stages are ntt_dev.h's eight-point column stages.
 enum MidKind { MID_UP, MID_DOWN, MID_RS, MID_RS2 };
 
 // Coefficients y of the sources (each in [0, its prime)) -> one destination's (d.a holds, by kind):
@@ -324,12 +156,6 @@ struct MidArgs {
   int digits, ns, ns_last;     // sources of a digit, and of the last one
   int n_all;                   // a digit's sources and destinations (MID_UP), or its destinations
   int n_split;
-};
-
-struct TwTables {
-  const uint64_t *psi, *psi_s, *ipsi, *ipsi_s;
-  const double *psi_f, *ipsi_f;
-  const Mod* mods;
 };
 
 // one source limb's columns to the map's input, in [0, modulus)
@@ -488,10 +314,6 @@ __global__ __launch_bounds__(64) void k_fwd_rows_final(const uint64_t* __restric
 }
 
 // ---- launches ------------------------------------------------------------------------------
-static TwTables tables(ckks_ctx* c) {
-  return TwTables{c->t.psi, c->t.psi_s, c->t.ipsi, c->t.ipsi_s, c->t.psi_f, c->t.ipsi_f, c->t.mods};
-}
-
 #define BY_LOGC_ROW(lc, X)                                       \
   switch (lc) {                                                  \
     case 4: X(4); break;                                         \
@@ -515,7 +337,7 @@ static TwTables tables(ckks_ctx* c) {
 template <class S>
 static void inv_rows(ckks_ctx* c, const S& src, int n_limbs, int n_polys) {
   const int lr = c->log_n - ntt_mid_log(c);
-  const TwTables tt = tables(c);
+  const TwTables tt = tw_tables(c);
 #define X(LC)                                                                                                       \
   hipLaunchKernelGGL((k_inv_rows<LC, S>), dim3((c->N >> LC) / row_cols<LC>(), n_limbs, n_polys), dim3(64), 0,       \
                      c->stream, src, c->log_n, tt.ipsi, tt.ipsi_s, tt.ipsi_f, tt.mods)
@@ -533,7 +355,7 @@ static int mid_split(ckks_ctx* c, int lc, int digits, int n_polys, int n_dst) {
 template <int KIND, int NS>
 static void mid(ckks_ctx* c, MidArgs m, int n_polys, int most) {
   const int lc = ntt_mid_log(c);
-  const TwTables tt = tables(c);
+  const TwTables tt = tw_tables(c);
   m.n_split = mid_split(c, lc, m.digits, n_polys, most);
 #define X(LC)                                                                                                 \
   hipLaunchKernelGGL((k_mid<LC, KIND, NS>), dim3((c->N >> LC) / MID_COLS, m.digits * m.n_split, n_polys),     \
@@ -578,7 +400,7 @@ void moddown_final(ckks_ctx* c, int level, const uint64_t* acc, uint64_t* conv, 
                    const FinalJob& one, int n) {
   const int l1 = level + 1, ext = l1 + c->alpha;
   const int lr = c->log_n - ntt_mid_log(c);
-  const TwTables tt = tables(c);
+  const TwTables tt = tw_tables(c);
   const MDK& k = c->mdk[level];
 #define X(LC)                                                                                                    \
   hipLaunchKernelGGL(k_fwd_rows_final<LC>, dim3((c->N >> LC) / row_cols<LC>(), l1, 2 * n), dim3(64), 0,          \

@@ -13,7 +13,8 @@
 // relinearisation key's tag is 0.
 #include <algorithm>
 
-#include "internal.h"
+#include "ks_common.h"
+#include "ntt_dev.h"
 
 namespace ficgcn {
 
@@ -43,48 +44,50 @@ __device__ void chacha_block(uint64_t seed, uint32_t n0, uint32_t n1, uint32_t n
   for (int i = 0; i < 16; ++i) out[i] = x[i] + s[i];
 }
 
-// one thread = one block = 4 coefficients of one limb; blockIdx.z = polynomial
-// z at out + z * poly_stride, drawn from the stream with nonce word a + z
+// the coefficients of one block
+__device__ __forceinline__ void uniform4(const uint32_t (&w)[16], const Mod& m, uint64_t (&v)[4]) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    v[u] = reduce128((uint64_t)w[4 * u + 2] | ((uint64_t)w[4 * u + 3] << 32),
+                     (uint64_t)w[4 * u] | ((uint64_t)w[4 * u + 1] << 32), m);
+}
+// dist 0 = ternary, 1 = CBD(21)
+__device__ __forceinline__ void small8(const uint32_t (&w)[16], int dist, int64_t (&v)[8]) {
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const uint64_t x = (uint64_t)w[2 * u] | ((uint64_t)w[2 * u + 1] << 32);
+    if (dist == 0) {
+      v[u] = (int64_t)(x % 3) - 1;
+    } else {
+      const uint64_t msk = (1ull << 21) - 1;
+      v[u] = (int64_t)__popcll(x & msk) - (int64_t)__popcll((x >> 21) & msk);
+    }
+  }
+}
+
+// one thread = one block = 4 coefficients of one limb
 __global__ void k_uniform(uint64_t* __restrict__ out, uint64_t seed, uint32_t kind, uint32_t a, uint32_t b0,
-                          LimbMap map, int log_n, const Mod* __restrict__ mods, size_t poly_stride) {
+                          LimbMap map, int log_n, const Mod* __restrict__ mods) {
   const size_t N = (size_t)1 << log_n;
   const uint32_t blk = blockIdx.x * SB + threadIdx.x;
   if ((size_t)blk * 4 >= N) return;
   const int i = blockIdx.y;
   const int mi = lm_mod(map, i);
-  out += blockIdx.z * poly_stride;
   uint32_t w[16];
-  chacha_block(seed, kind, a + blockIdx.z, b0 + (uint32_t)mi, blk, w);
+  chacha_block(seed, kind, a, b0 + (uint32_t)mi, blk, w);
   const Mod m = mods[mi];
-  for (int u = 0; u < 4; ++u) {
-    uint64_t lo = (uint64_t)w[4 * u] | ((uint64_t)w[4 * u + 1] << 32);
-    uint64_t hi = (uint64_t)w[4 * u + 2] | ((uint64_t)w[4 * u + 3] << 32);
-    out[i * N + (size_t)blk * 4 + u] = reduce128(hi, lo, m);
-  }
+  uint64_t v[4];
+  uniform4(w, m, v);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) out[i * N + (size_t)blk * 4 + u] = v[u];
 }
 
 void sample_uniform(ckks_ctx* c, uint64_t* out, uint64_t seed, uint32_t kind, uint32_t a, uint32_t b0, int n_limbs,
                     LimbMap map, uint32_t) {
   int nb = (c->N / 4 + SB - 1) / SB;
   hipLaunchKernelGGL(k_uniform, dim3(nb, n_limbs), dim3(SB), 0, c->stream, out, seed, kind, a, b0, map, c->log_n,
-                     c->t.mods, (size_t)0);
+                     c->t.mods);
   HIPCHECK(hipGetLastError());
-}
-
-void expand_seeded(ckks_ctx* c, uint64_t a_seed, uint32_t ct_id0, size_t count, int level, uint64_t* cts) {
-  const size_t N = c->N;
-  const int l1 = level + 1;
-  const size_t ct_words = 2 * (size_t)l1 * N;
-  const int nb = (int)((N / 4 + SB - 1) / SB);
-  constexpr size_t CHUNK = 4096;   // polynomials per launch (grid z)
-  for (size_t z0 = 0; z0 < count; z0 += CHUNK) {
-    const size_t nz = std::min(CHUNK, count - z0);
-    uint64_t* c1 = cts + z0 * ct_words + (size_t)l1 * N;
-    hipLaunchKernelGGL(k_uniform, dim3(nb, l1, (uint32_t)nz), dim3(SB), 0, c->stream, c1, a_seed, 4u,
-                       ct_id0 + (uint32_t)z0, 0u, lm_q(l1), c->log_n, c->t.mods, ct_words);
-    HIPCHECK(hipGetLastError());
-    ntt_fwd(c, c1, l1, lm_q(l1), (int)nz, ct_words);
-  }
 }
 
 // ---- bit-packed residues (transport of client words) ----
@@ -155,19 +158,12 @@ __global__ void k_small(uint64_t* __restrict__ out, uint64_t seed, uint32_t kind
   if ((size_t)blk * 8 >= N) return;
   uint32_t w[16];
   chacha_block(seed, kind, a, b, blk, w);
-  for (int u = 0; u < 8; ++u) {
-    uint64_t x = (uint64_t)w[2 * u] | ((uint64_t)w[2 * u + 1] << 32);
-    int64_t v;
-    if (dist == 0) {
-      v = (int64_t)(x % 3) - 1;
-    } else {
-      const uint64_t msk = (1ull << 21) - 1;
-      v = (int64_t)__popcll(x & msk) - (int64_t)__popcll((x >> 21) & msk);
-    }
-    for (int i = 0; i < n_limbs; ++i) {
-      uint64_t q = mods[lm_mod(map, i)].q;
-      out[i * N + (size_t)blk * 8 + u] = v >= 0 ? (uint64_t)v : q - (uint64_t)(-v);
-    }
+  int64_t v[8];
+  small8(w, dist, v);
+  for (int i = 0; i < n_limbs; ++i) {
+    const uint64_t q = mods[lm_mod(map, i)].q;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) out[i * N + (size_t)blk * 8 + u] = v[u] >= 0 ? (uint64_t)v[u] : q - (uint64_t)(-v[u]);
   }
 }
 
@@ -223,28 +219,159 @@ void keygen_swk(ckks_ctx* c, uint64_t seed, const uint64_t* s_ntt, const uint64_
   HIPCHECK(hipStreamSynchronize(c->stream));
 }
 
-// c0 = e - a s + m
-__global__ void k_enc(uint64_t* __restrict__ c0, const uint64_t* __restrict__ a, const uint64_t* __restrict__ s,
-                      const uint64_t* __restrict__ m, int log_n, const Mod* __restrict__ mods) {
-  const size_t N = (size_t)1 << log_n;
-  const size_t j = blockIdx.x * (size_t)SB + threadIdx.x;
+// ---- sampling inside the transform --------------------------------------------------------------
+// A forward transform begins with its column pass, and a tile of 16 columns takes 16 consecutive
+// coefficients of each row: whole blocks of the stream.  So the column pass draws its input instead of
+// reading it (a small polynomial's blocks once for every limb), and of an encryption the row pass takes the
+// rest: both polynomials' rows of a limb, then c0 = e - a s + m.
+// Bound by the stream's 20 rounds (1060 instructions a block of 4 coefficients).  64 uniform polynomials of 7
+// limbs at N = 2^16: 267 us, where drawing took 236 and the column pass 87.  One encryption of 7 limbs, bound by
+// launch latency: 13.5 + 9.5 us in two kernels, 46 us in seven.
+struct Draw {
+  uint64_t seed;
+  uint32_t kind, a;
+  int32_t uniform;   // else CBD(21)
+  int32_t pad;
+};
+// four coefficients as uniform4's, signed, for a prime of the fp64 range; r64 = 2^64 mod q.  A 64-bit half
+// hi 2^32 + lo comes down as (hi 2^32 reduced) + lo, below 0.51 q.
+__device__ __forceinline__ void uniform4_fp(const uint32_t (&w)[16], double r64, double qd, double qinv,
+                                            uint64_t (&v)[4]) {
+  auto half = [&](uint32_t hi, uint32_t lo) { return sred((double)hi * 4294967296.0, qd, qinv) + (double)lo; };
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    v[u] = f2b(sred(fmulmod_s(half(w[4 * u + 3], w[4 * u + 2]), r64, qd, qinv) + half(w[4 * u + 1], w[4 * u]), qd,
+                    qinv));
+}
+
+// polynomial z's stream has the second nonce word d.a + z: the first one from d0, the others from d1
+struct DrawSrc {
+  Draw d0, d1;
+  template <int LOGC, bool FP>
+  __device__ __forceinline__ void load(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC>& p, int mi, const Mod& m,
+                                       int z, const Tw& t, int log_n) const {
+    typedef MidGeo<LOGC> G;
+    const Draw d = z == 0 ? d0 : d1;
+    const uint32_t first = blockIdx.x * MID_COLS, nonce = d.a + (uint32_t)z;
+    auto row = [&](int e) { return s + (e + (e >> 3)) * MID_COLS; };
+    uint32_t w[16];
+    if (d.uniform) {
+      const double r64 = FP ? fmulmod_s(4294967296.0, 4294967296.0, t.qd, t.qinv) : 0.0;
+#pragma unroll 1
+      for (int at = threadIdx.x; at < G::C * (MID_COLS / 4); at += G::THREADS) {
+        const int e = at / (MID_COLS / 4), g = at % (MID_COLS / 4) * 4;
+        chacha_block(d.seed, d.kind, nonce, (uint32_t)mi, (((uint32_t)e << (log_n - LOGC)) + first + g) >> 2, w);
+        uint64_t v[4];
+        if (FP)
+          uniform4_fp(w, r64, t.qd, t.qinv, v);
+        else
+          uniform4(w, m, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) row(e)[g + k] = v[k];
+      }
+    } else {
+#pragma unroll 1
+      for (int at = threadIdx.x; at < G::C * (MID_COLS / 8); at += G::THREADS) {
+        const int e = at / (MID_COLS / 8), g = at % (MID_COLS / 8) * 8;
+        chacha_block(d.seed, d.kind, nonce, 0, (((uint32_t)e << (log_n - LOGC)) + first + g) >> 3, w);
+        int64_t v[8];
+        small8(w, 1, v);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          row(e)[g + k] = FP ? f2b((double)(int32_t)v[k]) : v[k] >= 0 ? (uint64_t)v[k] : m.q - (uint64_t)(-v[k]);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = s[p.a(u)];
+  }
+};
+
+void expand_seeded(ckks_ctx* c, uint64_t a_seed, uint32_t ct_id0, size_t count, int level, uint64_t* cts) {
+  const int l1 = level + 1;
+  const size_t ct_words = 2 * (size_t)l1 * c->N;
+  constexpr size_t CHUNK = 4096;   // polynomials per launch (grid z)
+  for (size_t z0 = 0; z0 < count; z0 += CHUNK) {
+    const size_t nz = std::min(CHUNK, count - z0);
+    uint64_t* c1 = cts + z0 * ct_words + (size_t)l1 * c->N;
+    const Draw d{a_seed, 4, ct_id0 + (uint32_t)z0, 1, 0};
+    src_cols(c, c1, ct_words, DrawSrc{d, d}, l1, lm_q(l1), (int)nz);
+    ntt_fwd_rows(c, c1, l1, lm_q(l1), (int)nz, ct_words);
+  }
+}
+
+// One wave a polynomial (0: e and then c0, 1: a), both on the same chunks
+template <int LOGC, bool FP>
+__device__ __forceinline__ void enc_rows_body(uint64_t* l, uint64_t* c0, uint64_t* c1, const uint64_t* s,
+                                              const uint64_t* m, const Mod& md, const Tw& t, int log_n) {
+  constexpr int COLS = row_cols<LOGC>();
+  typedef PassGeo<LOGC, COLS> G;
+  constexpr int H = G::EPT / 2;
+  const int poly = threadIdx.x >> 6;
+  const Place<LOGC, COLS, true> p(threadIdx.x & 63, blockIdx.x);
+  const uint64_t* in = poly ? c1 : c0;
+  uint64_t* const mine = l + poly * G::LDS_WORDS;
+  uint64_t x[G::EPT], sv[H], mv[H];
+#pragma unroll
+  for (int u = 0; u < G::EPT; ++u) x[u] = in[p.gidx(p.r + G::TPC * u, log_n)];
+  // each wave takes half of the last step's elements
+  auto elem = [&](int u) { return p.r + G::TPC * (u + poly * H); };
+#pragma unroll
+  for (int u = 0; u < H; ++u) {
+    sv[u] = s[p.gidx(elem(u), log_n)];
+    mv[u] = m[p.gidx(elem(u), log_n)];
+  }
+  fwd_core<LOGC, COLS, true, FP>(x, mine, p, t, log_n);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < G::EPT; ++u)
+    mine[p.sidx(p.r * G::EPT + u)] = FP ? from_fbits(f2b(canon(b2f(x[u]), t.qd))) : canon8(x[u], t.c, t.q);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < H; ++u) {
+    const uint32_t n = p.gidx(elem(u), log_n);
+    const uint64_t e = l[p.sidx(elem(u))], a = l[G::LDS_WORDS + p.sidx(elem(u))];
+    c1[n] = a;
+    c0[n] = add_mod(sub_mod(e, mul_mod(a, sv[u], md), t.q), mv[u], t.q);
+  }
+}
+
+template <int LOGC>
+__global__ __launch_bounds__(128) void k_enc_rows(uint64_t* __restrict__ ct, int l1, const uint64_t* __restrict__ s,
+                                                  const uint64_t* __restrict__ m, TwTables tt, int log_n) {
+  __shared__ uint64_t l[2 * PassGeo<LOGC, row_cols<LOGC>()>::LDS_WORDS];
   const int i = blockIdx.y;
-  const Mod md = mods[i];
-  const size_t o = i * N + j;
-  uint64_t v = sub_mod(c0[o], reduce128((u128)a[o] * s[o], md), md.q);
-  c0[o] = add_mod(v, m[o], md.q);
+  const Mod md = cld(tt.mods + i);
+  const size_t o = (size_t)i << log_n;
+  uint64_t* c0 = ct + o;
+  uint64_t* c1 = c0 + ((size_t)l1 << log_n);
+  const Tw t = make_tw(tt.psi, tt.psi_s, tt.psi_f, md.q, md.qinv, i, log_n);
+  if (fp_prime(md.q))
+    enc_rows_body<LOGC, true>(l, c0, c1, s + o, m + o, md, t, log_n);
+  else
+    enc_rows_body<LOGC, false>(l, c0, c1, s + o, m + o, md, t, log_n);
 }
 
 void encrypt_sym(ckks_ctx* c, const uint64_t* s_ntt, const uint64_t* m_ntt, int level, uint64_t seed, uint64_t a_seed,
                  uint32_t ct_id, uint64_t* ct) {
-  const size_t N = c->N;
   const int l1 = level + 1;
-  uint64_t* c0 = ct;
-  uint64_t* c1 = ct + (size_t)l1 * N;
-  expand_seeded(c, a_seed, ct_id, 1, level, ct);
-  sample_small_rns(c, c0, seed, 5, ct_id, 0, 1, l1, lm_q(l1));
-  ntt_fwd(c, c0, l1, lm_q(l1), 1, 0);
-  hipLaunchKernelGGL(k_enc, dim3(N / SB, l1), dim3(SB), 0, c->stream, c0, c1, s_ntt, m_ntt, c->log_n, c->t.mods);
+  src_cols(c, ct, (size_t)l1 * c->N, DrawSrc{Draw{seed, 5, ct_id, 0, 0}, Draw{a_seed, 4, ct_id - 1, 1, 0}}, l1,
+           lm_q(l1), 2);
+  const int lr = c->log_n - ntt_mid_log(c);
+  const TwTables tt = tw_tables(c);
+#define X(LC)                                                                                                       \
+  hipLaunchKernelGGL(k_enc_rows<LC>, dim3((c->N >> LC) / row_cols<LC>(), l1), dim3(128), 0, c->stream, ct, l1, s_ntt, \
+                     m_ntt, tt, c->log_n)
+  switch (lr) {
+    case 4: X(4); break;
+    case 5: X(5); break;
+    case 6: X(6); break;
+    case 7: X(7); break;
+    case 8: X(8); break;
+    case 9: X(9); break;
+    default: FICGCN_THROW(EINVAL_, "unsupported ring degree");
+  }
+#undef X
   HIPCHECK(hipGetLastError());
 }
 
