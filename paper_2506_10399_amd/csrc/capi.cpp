@@ -101,6 +101,7 @@ static void rotate_batch(ckks_ctx* ctx, const ckks_keys* ek, const uint64_t* con
   }
   for (auto& cp : copies) copy_d2d(ctx, cp.first, cp.second, (size_t)2 * l1 * N * 8);
   keyswitch_batch(ctx, (int)level, srcs, jobs, gouts, false);
+  if (!jobs.empty()) stream_sync(ctx);
 }
 
 extern "C" {

@@ -183,9 +183,7 @@ static bool strided(const uint64_t* const* p, size_t n, size_t min_words, const 
 
 template <typename T>
 static T* upload_ptrs(ckks_ctx* c, const std::vector<T>& v, int slot) {
-  T* d = (T*)dev_table(c, slot, v.data(), v.size() * sizeof(T));
-  stream_sync(c);
-  return d;
+  return (T*)dev_table(c, slot, v.data(), v.size() * sizeof(T));
 }
 
 static const uint64_t* rot_key(ckks_ctx* c, const ckks_keys* ek, int64_t step, uint64_t& g);
@@ -1176,6 +1174,7 @@ static void run_layer_eager(ckks_ctx* c, const ckks_keys* ek, ficgcn_plan* p, in
       moddown(c, acc, lo, out[i], d, 1, d + l1o * N);
     }
   }
+  if (mode == 1) stream_sync(c);
 }
 
 }  // namespace ficgcn

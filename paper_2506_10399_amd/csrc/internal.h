@@ -145,7 +145,7 @@ struct ckks_ctx {
   ficgcn::MidSrc* mid_src = nullptr;
   ficgcn::MidDst* mid_dst = nullptr;
   // grow-only scratch buffers by slot: ops.hip 1-9, sample/capi 10-29, gcn.cpp 30-49 and 70-79,
-  // ks_batch.hip 50-64 and 80-89, search.cpp 65-66 (a slot's memory moves when it grows, so one
+  // ks_batch.hip 50-59 and 80-84, search.cpp 65-66 (a slot's memory moves when it grows, so one
   // user per slot)
   std::vector<std::pair<void*, size_t>> scratch;
   // device tables of the GPU encoder (built on its first use)
@@ -158,6 +158,9 @@ struct ckks_ctx {
   // (re, then im) in host memory
   uint64_t* dec_inv = nullptr;
   double* dec_host = nullptr;    // [2][N/2]
+  // ring of small tables on their way to the device, and its device twin (dev_table)
+  uint8_t *stage_host = nullptr, *stage_dev = nullptr;
+  size_t stage_at = 0;
   // kernel timing (HIP events on `stream`), see ficgcn_profile_enable
   bool profiling = false;
   std::map<std::string, std::vector<std::pair<hipEvent_t, hipEvent_t>>> prof;
@@ -200,7 +203,8 @@ struct ProfScope {
 };
 
 // Scratch of `bytes` (context slot, or the recorder's buffer), a device copy
-// of a host table (slot + asynchronous copy, or the recorder's buffer), and
+// of a host table (the staging ring, a slot when it is large, or the recorder's
+// buffer; good for the launches that follow it, until 1 MB of further tables), and
 // a stream synchronisation that a replay being captured skips.
 void* dev_scratch(ckks_ctx* c, int slot, size_t bytes);
 void* dev_table(ckks_ctx* c, int slot, const void* host, size_t bytes);
@@ -254,6 +258,8 @@ void moddown(ckks_ctx* c, uint64_t* acc, int level, uint64_t* out, const uint64_
 void rescale_inplace(ckks_ctx* c, uint64_t* ct, int level);
 void tensor(ckks_ctx* c, const uint64_t* x, const uint64_t* y, uint64_t* d, int level);
 void copy_d2d(ckks_ctx* c, void* dst, const void* src, size_t bytes);
+// a multiple of 16 bytes, both 16-byte aligned; src may be pinned host memory
+void stage_copy(ckks_ctx* c, void* dst, const void* src, size_t bytes);
 // A (+)= acc (.) pt over the key basis Q_l then P (both components); pt null: A += acc
 void mac_ext(ckks_ctx* c, uint64_t* A, const uint64_t* acc, const uint64_t* pt, int level);
 // plaintexts on the key basis: [level+1+alpha][N], Q_l limbs then P, evaluation form

@@ -16,8 +16,10 @@
 // grouped final step replaces "write R switched ciphertexts, read them
 // back for a masked sum" by one read of acc and conv per switch.
 #include <algorithm>
+#include <cstring>
 #include <map>
 #include <numeric>
+#include <tuple>
 
 #include "fpmod.h"
 #include "ks_batch.h"
@@ -213,13 +215,23 @@ __global__ void k_ks_final(const uint64_t* __restrict__ acc, const uint64_t* __r
   gst(gd.out + o, add_mod(a, reduce128(s, md), q));
 }
 
-enum { S_KB_TMP = 50, S_KB_D, S_KB_ACC, S_KB_CONV, S_KB_JOBS, S_KB_SRC, S_KB_GRP, S_TB_JOBS, S_RS_PTR, S_RS_LAST,
-       S_RS_D, S_GM_TERMS, S_GM_START, S_GM_OUT, S_KB_RUNS };
-enum { S_GM_GRP = 89 };
+enum { S_KB_TMP = 50, S_KB_D, S_KB_ACC, S_KB_CONV, S_KB_JOBS, S_TB_JOBS, S_RS_PTR, S_RS_LAST, S_RS_D, S_GM_TERMS };
 
-template <typename T>
-static T* upload(ckks_ctx* c, int slot, const std::vector<T>& v) {
-  return (T*)dev_table(c, slot, v.data(), v.size() * sizeof(T));
+// Device copies of a launch group's tables, in one transfer (each on a 16-byte boundary)
+template <typename... T>
+static std::tuple<T*...> upload(ckks_ctx* c, int slot, const std::vector<T>&... v) {
+  size_t bytes = 0;
+  const size_t at[] = {[&](size_t n) {
+    const size_t o = bytes;
+    bytes += (n + 15) & ~(size_t)15;
+    return o;
+  }(v.size() * sizeof(T))...};
+  std::vector<uint8_t> h(bytes);
+  size_t k = 0;
+  (void)std::initializer_list<int>{((v.empty() ? (void)0 : (void)std::memcpy(h.data() + at[k], v.data(), v.size() * sizeof(T))), ++k, 0)...};
+  uint8_t* d = (uint8_t*)dev_table(c, slot, h.data(), bytes);
+  k = 0;
+  return std::tuple<T*...>{(T*)(d + at[k++])...};
 }
 
 // ModUp of a batch's sources (device table of U polynomials [l1][N]) into D [U][nd][ext][N]
@@ -319,8 +331,6 @@ void keyswitch_batch(ckks_ctx* c, int level, const std::vector<const uint64_t*>&
       }
     }
     const int U = (int)srcs.size(), R = (int)cj.size();
-    KSJob* jd = upload(c, S_KB_JOBS, cj);
-    const uint64_t* const* sd = upload(c, S_KB_SRC, srcs);
     // one unmasked switch per output: the last step is part of the transform before it
     std::vector<FinalJob> finals;
     bool single = fused_basis(c) && gds.size() == cj.size();
@@ -328,8 +338,9 @@ void keyswitch_batch(ckks_ctx* c, int level, const std::vector<const uint64_t*>&
     if (single)
       for (int r = 0; r < R; ++r)
         finals.push_back(FinalJob{gds[r].out, cj[r].add0, cj[r].add1, cj[r].g, gds[r].accumulate, 0});
-    GroupDesc* gd = single ? nullptr : upload(c, S_KB_GRP, gds);
-    FinalJob* fd = single ? upload(c, S_KB_GRP, finals) : nullptr;
+    std::vector<int> runs = key_runs(cj);
+    const int n_runs = (int)runs.size() - 1;
+    const auto [jd, sd, gd, fd, rd] = upload(c, S_KB_JOBS, cj, srcs, gds, finals, runs);
     uint64_t* tmp = (uint64_t*)dev_scratch(c, S_KB_TMP, (size_t)U * l1 * N * 8);
     uint64_t* D = (uint64_t*)dev_scratch(c, S_KB_D, (size_t)U * nd * ext * N * 8);
     uint64_t* acc = (uint64_t*)dev_scratch(c, S_KB_ACC, (size_t)R * 2 * ext * N * 8);
@@ -340,10 +351,7 @@ void keyswitch_batch(ckks_ctx* c, int level, const std::vector<const uint64_t*>&
     }
     {
       ProfScope pk(c, "keymac");
-      const std::vector<int> runs = key_runs(cj);
-      const int n_runs = (int)runs.size() - 1;
       if (n_runs < R && nd <= KR_MAXD) {   // some jobs share a key: each key read once per run
-        const int* rd = upload(c, S_KB_RUNS, runs);
         const dim3 grid(N / KB, ext, n_runs);
 #define KR_LAUNCH(NDV)                                                                                          \
   hipLaunchKernelGGL(k_keymac_runs<NDV>, grid, dim3(KB), 0, c->stream, acc, D, jd, rd, ext, l1, c->L, c->n_mod(), \
@@ -377,8 +385,6 @@ void keyswitch_batch(ckks_ctx* c, int level, const std::vector<const uint64_t*>&
         moddown_final(c, level, acc, conv, fd, FinalJob{}, R);
       }
     }
-    // the host lists of this chunk are released below and the device lists reused
-    stream_sync(c);
     a = b;
   }
   if (!accumulate)
@@ -796,7 +802,7 @@ __global__ void k_masked_final(const uint64_t* __restrict__ A, const uint64_t* _
   gst(out + o, accumulate ? add_mod(gld(out + o), v, q) : v);
 }
 
-enum { S_KM_A = 80, S_KM_CONV, S_KM_JOBS, S_KM_GRP, S_KM_OUT, S_KM_CGRP, S_KM_RUNS, S_KM_GL, S_KM_P };
+enum { S_KM_A = 80, S_KM_CONV, S_KM_JOBS, S_KM_OUT, S_KM_P };
 
 // rotations a launch takes: its LDS, and the sums' room (narrow words: 4095 products of 2^52; wide
 // ones: products of two words below 2^bits in 128 bits)
@@ -853,9 +859,7 @@ static void masked_uniform(ckks_ctx* c, int level, const std::vector<const uint6
       }
     }
     const int U = (int)srcs.size(), ng = gb - ga;
-    const UJob* jd = upload(c, S_KB_JOBS, list);
-    const USrc* ud = upload(c, S_KM_GL, us);
-    const uint64_t* const* sd = upload(c, S_KB_SRC, srcs);
+    const auto [jd, ud, sd] = upload(c, S_KB_JOBS, list, us, srcs);
     uint64_t* tmp = (uint64_t*)dev_scratch(c, S_KB_TMP, (size_t)U * l1 * N * 8);
     uint64_t* D = (uint64_t*)dev_scratch(c, S_KB_D, (size_t)U * nd * ext * N * 8);
     {
@@ -886,7 +890,6 @@ static void masked_uniform(ckks_ctx* c, int level, const std::vector<const uint6
         HIPCHECK(hipGetLastError());
       }
     }
-    stream_sync(c);
     ga = gb;
   }
 }
@@ -925,12 +928,11 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
     masked_uniform(c, level, sources, jobs, n_grp, A);
     std::vector<FinalJob> finals;
     for (uint64_t* o : outs) finals.push_back(FinalJob{o, nullptr, nullptr, 1, accumulate ? 1 : 0, 0});
-    const FinalJob* fd = upload(c, S_KM_OUT, finals);
+    const auto [fd] = upload(c, S_KM_OUT, finals);
     uint64_t* conv = (uint64_t*)dev_scratch(c, S_KM_CONV, (size_t)n_grp * 2 * l1 * N * 8);
     ProfScope pd(c, "moddown");
     moddown_polys(c, level, A, 2 * n_grp, conv, false);
     moddown_final(c, level, A, conv, fd, FinalJob{}, n_grp);
-    stream_sync(c);
     return;
   }
   zero_fill(c, A, (size_t)n_grp * 2 * ext * N);
@@ -972,9 +974,13 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
       }
     }
     const int U = (int)srcs.size();
-    KSJob* jd = upload(c, S_KB_JOBS, cj);
-    const uint64_t* const* sd = upload(c, S_KB_SRC, srcs);
-    GroupDesc* gd = upload(c, S_KM_CGRP, gds);
+    // by key: runs of jobs that share one, and each job's output
+    std::vector<int> runs, kgl;
+    if (by_key) {
+      runs = key_runs(cj);
+      for (const KSJob& jb : cj) kgl.push_back(jb.grp);
+    }
+    const auto [jd, sd, gd, rd, gld_] = upload(c, S_KB_JOBS, cj, srcs, gds, runs, kgl);
     uint64_t* tmp = (uint64_t*)dev_scratch(c, S_KB_TMP, (size_t)U * l1 * N * 8);
     uint64_t* D = (uint64_t*)dev_scratch(c, S_KB_D, (size_t)U * nd * ext * N * 8);
     {
@@ -987,13 +993,8 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
       const int n_jb = (int)(N / KB), ng = (int)gds.size();
       if (by_key) {
         // each key read once for every output that uses it; runs split in segments for parallelism
-        const std::vector<int> runs = key_runs(cj);
         const int n_runs = (int)runs.size() - 1;
         const int n_seg = std::max(1, std::min(32, n_runs / 8));
-        std::vector<int> kgl(cj.size());
-        for (size_t r = 0; r < cj.size(); ++r) kgl[r] = cj[r].grp;
-        const int* rd = upload(c, S_KM_RUNS, runs);
-        const int* gld_ = upload(c, S_KM_GL, kgl);
         uint64_t* P = (uint64_t*)dev_scratch(c, S_KM_P, (size_t)n_seg * ng * 2 * ext * N * 8);
         const dim3 grid(n_jb, ext, n_seg);
         int fq = 1;   // the Q limbs in fp64 residues when every Q prime of the level lies in (2^49, 2^50)
@@ -1031,7 +1032,6 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
       }
       HIPCHECK(hipGetLastError());
     }
-    stream_sync(c);
     a = b;
   }
   // one ModDown per output: P limbs to coefficient form, rounded conversion,
@@ -1045,15 +1045,12 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
       if (mg[g].end == 0) mg[g].start = (int)r;
       mg[g].end = (int)r + 1;
     }
-    KSJob* jall = upload(c, S_KM_JOBS, jobs);
-    MaskGroup* mgd = upload(c, S_KM_GRP, mg);
-    uint64_t* const* od = upload(c, S_KM_OUT, outs);
+    const auto [jall, mgd, od] = upload(c, S_KM_JOBS, jobs, mg, outs);
     uint64_t* conv = (uint64_t*)dev_scratch(c, S_KM_CONV, (size_t)n_grp * 2 * l1 * N * 8);
     moddown_conv_batch(c, level, A, 2 * n_grp, k, conv);
     hipLaunchKernelGGL(k_masked_final, dim3(N / KB, l1, 2 * n_grp), dim3(KB), 0, c->stream, A, conv, ext, l1, k, jall,
                        mgd, od, accumulate ? 1 : 0, c->log_n, c->t.mods);
     HIPCHECK(hipGetLastError());
-    stream_sync(c);
   }
 }
 
@@ -1075,11 +1072,10 @@ __global__ void k_tensor_batch(const TensorJob* __restrict__ jobs, int l1, int l
 
 void tensor_batch(ckks_ctx* c, int level, const std::vector<TensorJob>& jobs) {
   if (jobs.empty()) return;
-  TensorJob* jd = upload(c, S_TB_JOBS, jobs);
+  const auto [jd] = upload(c, S_TB_JOBS, jobs);
   hipLaunchKernelGGL(k_tensor_batch, dim3(c->N / KB, level + 1, jobs.size()), dim3(KB), 0, c->stream, jd, level + 1,
                      c->log_n, c->t.mods);
   HIPCHECK(hipGetLastError());
-  stream_sync(c);
 }
 
 // c'_i = (c_i + d_i) q_l^-1, compacted in place from [2][l+1][N] to [2][l][N].
@@ -1107,14 +1103,13 @@ void rescale_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
   ProfScope ps(c, "rescale");
   const size_t N = c->N;
   const int n = (int)cts.size();
-  uint64_t* const* cd = upload(c, S_RS_PTR, cts);
+  const auto [cd] = upload(c, S_RS_PTR, cts);
   uint64_t* last = (uint64_t*)dev_scratch(c, S_RS_LAST, (size_t)2 * n * N * 8);
   uint64_t* d = (uint64_t*)dev_scratch(c, S_RS_D, (size_t)2 * n * level * N * 8);
   const RSK& k = c->rsk[level];
   rescale_prep(c, level, cd, nullptr, n, last, d);
   hipLaunchKernelGGL(k_rs_final, dim3(N / KB, 2 * n), dim3(KB), 0, c->stream, cd, d, level, k, c->log_n, c->t.mods);
   HIPCHECK(hipGetLastError());
-  stream_sync(c);
 }
 
 // Two rescales in one call, c'' = round(round(c / q_l) / q_{l-1}), word for
@@ -1162,7 +1157,7 @@ void rescale2_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
   ProfScope ps(c, "rescale");
   const size_t N = c->N;
   const int n = (int)cts.size();
-  uint64_t* const* cd = upload(c, S_RS_PTR, cts);
+  const auto [cd] = upload(c, S_RS_PTR, cts);
   uint64_t* last = (uint64_t*)dev_scratch(c, S_RS_LAST, (size_t)2 * n * 2 * N * 8);
   uint64_t* f = (uint64_t*)dev_scratch(c, S_RS_D, (size_t)2 * n * (level - 1) * N * 8);
   RSK2 k{};
@@ -1183,7 +1178,6 @@ void rescale2_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
   rescale2_prep(c, level, cd, n, last, f);
   hipLaunchKernelGGL(k_rs2_final, dim3(N / KB, 2 * n), dim3(KB), 0, c->stream, cd, f, level, k, c->log_n, c->t.mods);
   HIPCHECK(hipGetLastError());
-  stream_sync(c);
 }
 
 // outs[g] (+)= sum over the terms of group g of ct (.) pt, or ct when pt is null
@@ -1266,9 +1260,7 @@ void group_mac(ckks_ctx* c, int level, const std::vector<std::vector<MacTerm>>& 
   }
   for (uint64_t* o : outs)
     if (!o) FICGCN_THROW(EINVAL_, "null output");
-  MacTerm* td = upload(c, S_GM_TERMS, flat);
-  int* sd = upload(c, S_GM_START, start);
-  uint64_t* const* od = upload(c, S_GM_OUT, outs);
+  const auto [td, sd, od] = upload(c, S_GM_TERMS, flat, start, outs);
   if (groups.size() > 65535) FICGCN_THROW(EINVAL_, "too many groups in one launch");
   const int n_jb = c->N / KB, ng = (int)groups.size();
   const bool xcd = n_jb % 8 == 0 && (size_t)n_jb * ng < ((size_t)1 << 31);
@@ -1276,7 +1268,6 @@ void group_mac(ckks_ctx* c, int level, const std::vector<std::vector<MacTerm>>& 
   hipLaunchKernelGGL(k_group_mac, grid, dim3(KB), 0, c->stream, td, sd, od, level + 1, accumulate ? 1 : 0, c->log_n, ng,
                      xcd ? 1 : 0, c->t.mods);
   HIPCHECK(hipGetLastError());
-  stream_sync(c);
 }
 
 
@@ -1785,10 +1776,7 @@ void group_mac_np(ckks_ctx* c, int level, int np, const std::vector<std::vector<
     LdsForm f;
     const size_t g1 = lds_form(c, level, np, groups, g0, f);
     if (g1 == g0 || f.terms.size() < (size_t)GL_MIN_TERMS) break;
-    const uint64_t* const* tup = upload(c, S_GM_TERMS, f.tuples);
-    const uint32_t* td = upload(c, S_GM_START, f.terms);
-    NpGroup* gd = upload(c, S_GM_GRP, f.groups);
-    uint64_t* const* od = upload(c, S_GM_OUT, outs);
+    const auto [tup, td, gd, od] = upload(c, S_GM_TERMS, f.tuples, f.terms, f.groups, outs);
     ProfScope ps(c, "bsgs_inner");   // the launch alone (its tables are uploaded above)
     const dim3 lgrid(c->N / GL_COEF, level + 1);
     const int n_tup = (int)(f.tuples.size() / np), nt = (int)f.terms.size(), nlg = (int)f.groups.size();
@@ -1802,7 +1790,6 @@ void group_mac_np(ckks_ctx* c, int level, int np, const std::vector<std::vector<
 #undef GL_LAUNCH
     HIPCHECK(hipGetLastError());
     ps.stop();
-    stream_sync(c);
     g0 = g1;
   }
   if (g0) {   // the rest, if any, in the form below
@@ -1811,9 +1798,7 @@ void group_mac_np(ckks_ctx* c, int level, int np, const std::vector<std::vector<
                  std::vector<uint64_t*>(outs.begin() + g0 * np, outs.end()), accumulate);
     return;
   }
-  MacTermNP* td = upload(c, S_GM_TERMS, flat);
-  int* sd = upload(c, S_GM_START, start);
-  uint64_t* const* od = upload(c, S_GM_OUT, outs);
+  const auto [td, sd, od] = upload(c, S_GM_TERMS, flat, start, outs);
   ProfScope ps(c, "bsgs_inner");   // the launch alone (its tables are uploaded above)
 #define GM_LAUNCH(NPV, AV)                                                                                     \
   hipLaunchKernelGGL((k_group_mac_np<NPV, AV>), grid, dim3(GM_TB), 0, c->stream, td, sd, od, level + 1, acc, \
@@ -1834,7 +1819,6 @@ void group_mac_np(ckks_ctx* c, int level, int np, const std::vector<std::vector<
 #undef GM_LAUNCH
   HIPCHECK(hipGetLastError());
   ps.stop();
-  stream_sync(c);
 }
 
 }  // namespace ficgcn

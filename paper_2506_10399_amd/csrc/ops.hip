@@ -299,6 +299,18 @@ void mac_ext(ckks_ctx* c, uint64_t* A, const uint64_t* acc, const uint64_t* pt, 
   HIPCHECK(hipGetLastError());
 }
 
+__global__ void k_stage(ulonglong2* __restrict__ dst, const ulonglong2* __restrict__ src, size_t n) {
+  const size_t j = blockIdx.x * (size_t)EW + threadIdx.x;
+  if (j < n) dst[j] = src[j];
+}
+
+void stage_copy(ckks_ctx* c, void* dst, const void* src, size_t bytes) {
+  const size_t n = bytes / 16;
+  hipLaunchKernelGGL(k_stage, dim3((n + EW - 1) / EW), dim3(EW), 0, c->stream, (ulonglong2*)dst,
+                     (const ulonglong2*)src, n);
+  HIPCHECK(hipGetLastError());
+}
+
 void copy_d2d(ckks_ctx* c, void* dst, const void* src, size_t bytes) {
   HIPCHECK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->stream));
 }

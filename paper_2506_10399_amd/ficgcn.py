@@ -8,6 +8,7 @@ is no CPU fallback.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import List, Optional, Sequence
@@ -217,10 +218,14 @@ def _ptr(x) -> int:
 
 
 def _ptr_array(xs) -> ctypes.Array:
-    arr = (c_vp * max(1, len(xs)))()
-    for i, x in enumerate(xs):
-        arr[i] = _ptr(x)
-    return arr
+    # tensors alone, the common case, at 0.1 us each (a layer may take 3000): a third of asking each for its kind
+    try:
+        a = array.array("Q", [x.data_ptr() for x in xs])
+    except AttributeError:
+        a = array.array("Q", [_ptr(x) or 0 for x in xs])
+    if not a:
+        a.append(0)
+    return (c_vp * len(a)).from_buffer(a)
 
 
 class Context:
