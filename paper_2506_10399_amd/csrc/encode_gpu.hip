@@ -152,8 +152,8 @@ __global__ __launch_bounds__(ET) void k_enc_fft(cplx* __restrict__ v, Io io, con
 struct CoefSrc {
   const int64_t* m;
   const Fold25* folds;
-  template <int LOGC, bool FP>
-  __device__ __forceinline__ void load(uint64_t (&x)[8], uint64_t*, const MidPlace<LOGC>& p, int mi, const Mod&, int z,
+  template <int LOGC, bool FP, int COLS>
+  __device__ __forceinline__ void load(uint64_t (&x)[8], uint64_t*, const MidPlace<LOGC, COLS>& p, int mi, const Mod&, int z,
                                        const Tw& t, int log_n) const {
     const int64_t* a = m + ((size_t)z << log_n) + p.unit;
     const uint64_t one_s = FP ? 0 : cld(&folds[mi].one_s);

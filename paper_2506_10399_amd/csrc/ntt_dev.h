@@ -338,31 +338,31 @@ __device__ __forceinline__ void inv_core(uint64_t (&x)[E], uint64_t* s,
 // times 16 columns are at most 64 lanes).  LDS is double buffered: the next transform's stores
 // cannot meet the previous one's loads, which every wave has done before the barrier between.
 constexpr int MID_COLS = 16;
-template <int LOGC>
+template <int LOGC, int COLS = MID_COLS>
 struct MidGeo {
   static constexpr int C = 1 << LOGC;
   static constexpr int EPT = 8;
   static constexpr int TPC = C / 8;
   static constexpr int S = TPC > 8 ? TPC / 8 : 1;
-  static constexpr int THREADS = TPC * MID_COLS;
-  static constexpr int BUF = MID_COLS * (C + C / 8);   // a pad row per eight spreads layout C over the banks
+  static constexpr int THREADS = TPC * COLS;
+  static constexpr int BUF = COLS * (C + C / 8);   // a pad row per eight spreads layout C over the banks
 };
-// LDS word of element e: (e + e / 8) 16 + column.  In every layout that is a base of the thread plus
+// LDS word of element e: (e + e / 8) COLS + column.  In every layout that is a base of the thread plus
 // a constant of u (a layout's steps never carry the first element's remainder past a row of eight).
-template <int LOGC>
+template <int LOGC, int COLS = MID_COLS>
 struct MidPlace {
-  typedef MidGeo<LOGC> G;
+  typedef MidGeo<LOGC, COLS> G;
   int r, unit, e0b, sa, sb, sc;
   __device__ __forceinline__ MidPlace(int tid, int block)
-      : r(tid / MID_COLS), unit(block * MID_COLS + tid % MID_COLS), e0b((r / G::S) * (8 * G::S) + r % G::S) {
-    const int col = tid % MID_COLS;
-    sa = (r + (r >> 3)) * MID_COLS + col;
-    sb = (e0b + (r / G::S) * G::S) * MID_COLS + col;
-    sc = 9 * r * MID_COLS + col;
+      : r(tid / COLS), unit(block * COLS + tid % COLS), e0b((r / G::S) * (8 * G::S) + r % G::S) {
+    const int col = tid % COLS;
+    sa = (r + (r >> 3)) * COLS + col;
+    sb = (e0b + (r / G::S) * G::S) * COLS + col;
+    sc = 9 * r * COLS + col;
   }
-  __device__ __forceinline__ int a(int u) const { return sa + (G::TPC * u + ((G::TPC * u) >> 3)) * MID_COLS; }
-  __device__ __forceinline__ int b(int u) const { return sb + (G::S * u + ((G::S * u) >> 3)) * MID_COLS; }
-  __device__ __forceinline__ int c(int v) const { return sc + v * MID_COLS; }
+  __device__ __forceinline__ int a(int u) const { return sa + (G::TPC * u + ((G::TPC * u) >> 3)) * COLS; }
+  __device__ __forceinline__ int b(int u) const { return sb + (G::S * u + ((G::S * u) >> 3)) * COLS; }
+  __device__ __forceinline__ int c(int v) const { return sc + v * COLS; }
   // word of element 8 r + v of a limb: v's part is the same for every thread
   __device__ __forceinline__ uint32_t word(int log_n) const { return ((uint32_t)(8 * r) << (log_n - LOGC)) + unit; }
   __device__ __forceinline__ size_t row(int v, int log_n) const { return (size_t)v << (log_n - LOGC); }
@@ -422,18 +422,18 @@ __device__ __forceinline__ void wave_order() {
 // layout A -> layout C, forward stages; s: this transform's LDS buffer.  In fp64 each layout's
 // twiddles are requested before the wait of the layout before it, `first` (layout B's, or C's when
 // there is no B) before the map; the integer form's, twice as many registers, where they are used.
-template <int LOGC, bool FP>
-__device__ __forceinline__ void mid_fwd_first(MidTw<FP>& m, const MidPlace<LOGC>& p, const Tw& t) {
-  typedef MidGeo<LOGC> G;
+template <int LOGC, bool FP, int COLS>
+__device__ __forceinline__ void mid_fwd_first(MidTw<FP>& m, const MidPlace<LOGC, COLS>& p, const Tw& t) {
+  typedef MidGeo<LOGC, COLS> G;
   if (G::S > 1)
     mid_tw<LOGC, FP, 3, (G::S > 1 ? 6 : 3), G::S, false>(m, p.e0b, t);
   else
     mid_tw<LOGC, FP, 3, (G::S > 1 ? 3 : LOGC), 1, false>(m, 8 * p.r, t);
 }
-template <int LOGC, bool FP>
-__device__ __forceinline__ void mid_fwd(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC>& p, const Tw& t,
+template <int LOGC, bool FP, int COLS>
+__device__ __forceinline__ void mid_fwd(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC, COLS>& p, const Tw& t,
                                         MidTw<FP>& first) {
-  typedef MidGeo<LOGC> G;
+  typedef MidGeo<LOGC, COLS> G;
   {
     MidTw<FP> a;
     mid_tw<LOGC, FP, 0, 3, G::TPC, true>(a, 0, t);
@@ -463,9 +463,9 @@ __device__ __forceinline__ void mid_fwd(uint64_t (&x)[8], uint64_t* s, const Mid
   }
 }
 // layout C -> layout A, inverse stages
-template <int LOGC, bool FP>
-__device__ __forceinline__ void mid_inv(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC>& p, const Tw& t) {
-  typedef MidGeo<LOGC> G;
+template <int LOGC, bool FP, int COLS>
+__device__ __forceinline__ void mid_inv(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC, COLS>& p, const Tw& t) {
+  typedef MidGeo<LOGC, COLS> G;
   constexpr int SC = G::S > 1 ? 6 : 3;   // first stage of layout C
   MidTw<FP> c, b;
   mid_tw<LOGC, FP, SC, LOGC, 1, false>(c, 8 * p.r, t);
@@ -493,14 +493,14 @@ __device__ __forceinline__ void mid_inv(uint64_t (&x)[8], uint64_t* s, const Mid
 // A forward column pass whose input a functor makes: src.load<LOGC, FP>(x, s, p, limb's modulus index, Mod,
 // poly, t, log_n) fills x in layout A, in (-q, q) (fp64) or [0, 8q).  It may use the LDS buffer s if each thread
 // ends with its own words of layout A (which are then its to overwrite).  Limb i of polynomial z goes to out + z * stride + i N, half transformed.
-template <int LOGC, class S>
-__global__ __launch_bounds__((1 << LOGC) / 8 * MID_COLS) void k_src_cols(uint64_t* __restrict__ out, size_t stride, S src,
+template <int LOGC, int COLS, class S>
+__global__ __launch_bounds__((1 << LOGC) / 8 * COLS) void k_src_cols(uint64_t* __restrict__ out, size_t stride, S src,
                                                                         LimbMap map, TwTables tt, int log_n) {
-  typedef MidGeo<LOGC> G;
+  typedef MidGeo<LOGC, COLS> G;
   __shared__ uint64_t s[G::BUF];
   const int i = blockIdx.y, z = blockIdx.z, mi = lm_mod(map, i);
   const Mod m = cld(tt.mods + mi);
-  const MidPlace<LOGC> p(threadIdx.x, blockIdx.x);
+  const MidPlace<LOGC, COLS> p(threadIdx.x, blockIdx.x);
   const Tw t = make_tw(tt.psi, tt.psi_s, tt.psi_f, m.q, m.qinv, mi, log_n);
   uint64_t* a = out + z * stride + ((size_t)i << log_n) + p.word(log_n);
   uint64_t x[8];
@@ -521,18 +521,28 @@ __global__ __launch_bounds__((1 << LOGC) / 8 * MID_COLS) void k_src_cols(uint64_
 template <class S>
 static void src_cols(ckks_ctx* c, uint64_t* out, size_t stride, const S& src, int n_limbs, LimbMap map, int n_polys) {
   const TwTables tt = tw_tables(c);
-#define X(LC)                                                                                                       \
-  hipLaunchKernelGGL((k_src_cols<LC, S>), dim3((c->N >> LC) / MID_COLS, n_limbs, n_polys),                          \
-                     dim3((1 << LC) / 8 * MID_COLS), 0, c->stream, out, stride, src, map, tt, c->log_n)
-  switch (ntt_mid_log(c)) {
-    case 4: X(4); break;
-    case 5: X(5); break;
+  // half the columns a workgroup (64-byte runs) where there would be less than two workgroups a CU: one encryption's
+  // 224 workgroups of 512 threads at N = 2^16 took 13.5 us, 448 of 256 take 12.1
+  const int lc = ntt_mid_log(c);
+  const bool narrow = lc >= 6 && (size_t)((c->N >> lc) / MID_COLS) * n_limbs * n_polys < 512;
+#define Y(LC, CO)                                                                                                   \
+  hipLaunchKernelGGL((k_src_cols<LC, CO, S>), dim3((c->N >> LC) / (CO), n_limbs, n_polys), dim3((1 << LC) / 8 * (CO)), 0, \
+                     c->stream, out, stride, src, map, tt, c->log_n)
+#define X(LC)           \
+  if (narrow)           \
+    Y(LC, MID_COLS / 2); \
+  else                  \
+    Y(LC, MID_COLS)
+  switch (lc) {
+    case 4: Y(4, MID_COLS); break;
+    case 5: Y(5, MID_COLS); break;
     case 6: X(6); break;
     case 7: X(7); break;
     case 8: X(8); break;
     default: FICGCN_THROW(EINVAL_, "unsupported ring degree");
   }
 #undef X
+#undef Y
   HIPCHECK(hipGetLastError());
 }
 

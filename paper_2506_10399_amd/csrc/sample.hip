@@ -220,13 +220,13 @@ void keygen_swk(ckks_ctx* c, uint64_t seed, const uint64_t* s_ntt, const uint64_
 }
 
 // ---- sampling inside the transform --------------------------------------------------------------
-// A forward transform begins with its column pass, and a tile of 16 columns takes 16 consecutive
+// A forward transform begins with its column pass, and a tile of 8 or 16 columns takes as many consecutive
 // coefficients of each row: whole blocks of the stream.  So the column pass draws its input instead of
 // reading it (a small polynomial's blocks once for every limb), and of an encryption the row pass takes the
 // rest: both polynomials' rows of a limb, then c0 = e - a s + m.
 // Bound by the stream's 20 rounds (1060 instructions a block of 4 coefficients).  64 uniform polynomials of 7
 // limbs at N = 2^16: 267 us, where drawing took 236 and the column pass 87.  One encryption of 7 limbs, bound by
-// launch latency: 13.5 + 9.5 us in two kernels, 46 us in seven.
+// launch latency: 12.1 + 9.5 us in two kernels, 46 us in seven.
 struct Draw {
   uint64_t seed;
   uint32_t kind, a;
@@ -247,19 +247,19 @@ __device__ __forceinline__ void uniform4_fp(const uint32_t (&w)[16], double r64,
 // polynomial z's stream has the second nonce word d.a + z: the first one from d0, the others from d1
 struct DrawSrc {
   Draw d0, d1;
-  template <int LOGC, bool FP>
-  __device__ __forceinline__ void load(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC>& p, int mi, const Mod& m,
+  template <int LOGC, bool FP, int COLS>
+  __device__ __forceinline__ void load(uint64_t (&x)[8], uint64_t* s, const MidPlace<LOGC, COLS>& p, int mi, const Mod& m,
                                        int z, const Tw& t, int log_n) const {
-    typedef MidGeo<LOGC> G;
+    typedef MidGeo<LOGC, COLS> G;
     const Draw d = z == 0 ? d0 : d1;
-    const uint32_t first = blockIdx.x * MID_COLS, nonce = d.a + (uint32_t)z;
-    auto row = [&](int e) { return s + (e + (e >> 3)) * MID_COLS; };
+    const uint32_t first = blockIdx.x * COLS, nonce = d.a + (uint32_t)z;
+    auto row = [&](int e) { return s + (e + (e >> 3)) * COLS; };
     uint32_t w[16];
     if (d.uniform) {
       const double r64 = FP ? fmulmod_s(4294967296.0, 4294967296.0, t.qd, t.qinv) : 0.0;
 #pragma unroll 1
-      for (int at = threadIdx.x; at < G::C * (MID_COLS / 4); at += G::THREADS) {
-        const int e = at / (MID_COLS / 4), g = at % (MID_COLS / 4) * 4;
+      for (int at = threadIdx.x; at < G::C * (COLS / 4); at += G::THREADS) {
+        const int e = at / (COLS / 4), g = at % (COLS / 4) * 4;
         chacha_block(d.seed, d.kind, nonce, (uint32_t)mi, (((uint32_t)e << (log_n - LOGC)) + first + g) >> 2, w);
         uint64_t v[4];
         if (FP)
@@ -271,8 +271,8 @@ struct DrawSrc {
       }
     } else {
 #pragma unroll 1
-      for (int at = threadIdx.x; at < G::C * (MID_COLS / 8); at += G::THREADS) {
-        const int e = at / (MID_COLS / 8), g = at % (MID_COLS / 8) * 8;
+      for (int at = threadIdx.x; at < G::C * (COLS / 8); at += G::THREADS) {
+        const int e = at / (COLS / 8), g = at % (COLS / 8) * 8;
         chacha_block(d.seed, d.kind, nonce, 0, (((uint32_t)e << (log_n - LOGC)) + first + g) >> 3, w);
         int64_t v[8];
         small8(w, 1, v);
