@@ -552,7 +552,7 @@ def headline_roofline(args, prof, info, prm, bsgs=None):
     combination pass over the client's ciphertext words, the longest single launch):
     algorithmic bytes per launch over its mean launch time from HIP events on the context's
     stream; traffic from the committed counter runs.  The SpIntra-CA layer's
-    baby-step/giant-step inner sums (k_group_mac_np, the second longest) are given beside it
+    baby-step/giant-step inner sums (k_group_mac_lds, the second longest) are given beside it
     on the same terms."""
     N = 1 << prm["log_n"]
     d0 = info[0]
@@ -572,7 +572,7 @@ def headline_roofline(args, prof, info, prm, bsgs=None):
         b_ms = ms_b / n_b
         b_ach = alg / (b_ms * 1e-3) / 1e9
         out["bsgs_inner_sums"] = dict(
-            kernel="k_group_mac_np (SpIntra-CA baby-step/giant-step inner sums, masks shared by the packed "
+            kernel="k_group_mac_lds (SpIntra-CA baby-step/giant-step inner sums, masks shared by the packed "
                    "ciphertexts)", bound="hbm", achieved=round(b_ach, 1), peak=HBM_PEAK_GBS, unit="GB/s",
             frac=round(b_ach / HBM_PEAK_GBS, 4),
             traffic=measured_traffic("group_mac_np_pubmed_traffic.json", "ks_batch.hip"),
