@@ -575,7 +575,7 @@ def headline_roofline(args, prof, info, prm, bsgs=None):
             kernel="k_group_mac_lds (SpIntra-CA baby-step/giant-step inner sums, masks shared by the packed "
                    "ciphertexts)", bound="hbm", achieved=round(b_ach, 1), peak=HBM_PEAK_GBS, unit="GB/s",
             frac=round(b_ach / HBM_PEAK_GBS, 4),
-            traffic=measured_traffic("group_mac_np_pubmed_traffic.json", "ks_batch.hip"),
+            traffic=measured_traffic("group_mac_lds_pubmed_traffic.json", "ks_batch.hip"),
             alg_bytes_per_launch=alg, avg_launch_ms=b_ms, launches=n_b, launches_per_step=per_step)
     return out
 
