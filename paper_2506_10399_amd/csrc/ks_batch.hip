@@ -813,15 +813,22 @@ static int ku_rotations(ckks_ctx* c, int nd) {
   return most;
 }
 
-// Every output's list of (key, Galois element, plaintext) is the first one's, and has its add0s
-static bool uniform_jobs(const std::vector<KSJob>& jobs, int n_grp) {
-  if (n_grp < 1 || jobs.empty() || jobs.size() % n_grp) return false;
+// The sources of the output that has the most, where every output's list of (key, Galois element,
+// plaintext) is the first one's and has its add0s; 0 where it is not
+static size_t uniform_jobs(const std::vector<KSJob>& jobs, int n_grp, size_t n_sources) {
+  if (n_grp < 1 || jobs.empty() || jobs.size() % n_grp) return 0;
   const size_t R = jobs.size() / n_grp;
+  std::vector<int> seen(n_sources, -1);   // the last output that read a source
+  size_t most = 0, n = 0;
   for (size_t k = 0; k < jobs.size(); ++k) {
     const KSJob &a = jobs[k], &b = jobs[k % R];
-    if (a.grp != (int)(k / R) || a.key != b.key || a.g != b.g || a.pt != b.pt || !a.add0) return false;
+    if (a.grp != (int)(k / R) || a.key != b.key || a.g != b.g || a.pt != b.pt || !a.add0) return 0;
+    if (k % R == 0) n = 0;
+    if (seen[a.src] != a.grp) ++n;
+    seen[a.src] = a.grp;
+    most = std::max(most, n);
   }
-  return true;
+  return most;
 }
 
 // The masked sums of outputs that share their list: A [n_grp][2][ext][N], first polynomials included
@@ -924,7 +931,11 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
   ProfScope ps(c, "ks_masked");
   // one accumulator on the key basis per output, summed over every chunk
   uint64_t* A = (uint64_t*)dev_scratch(c, S_KM_A, (size_t)n_grp * 2 * ext * N * 8);
-  if (fused_basis(c) && !by_key && nd <= KR_MAXD && uniform_jobs(jobs, n_grp)) {
+  const size_t per_src = (size_t)(nd * ext + l1) * N * 8;
+  // an output's sources lie in one chunk there, so they have to fit it (giant steps bring one a rotation: 140
+  // of them at N = 2^16 and 16 limbs are 11.7 GB)
+  const size_t n_src = fused_basis(c) && !by_key && nd <= KR_MAXD ? uniform_jobs(jobs, n_grp, sources.size()) : 0;
+  if (n_src == 1 || (n_src && n_src * per_src <= KS_BUDGET)) {
     masked_uniform(c, level, sources, jobs, n_grp, A);
     std::vector<FinalJob> finals;
     for (uint64_t* o : outs) finals.push_back(FinalJob{o, nullptr, nullptr, 1, accumulate ? 1 : 0, 0});
@@ -937,7 +948,6 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
   }
   zero_fill(c, A, (size_t)n_grp * 2 * ext * N);
   const size_t per_job = 0;   // a job's products go straight into its output's accumulator
-  const size_t per_src = (size_t)(nd * ext + l1) * N * 8;
   size_t a = 0;
   while (a < jl.size()) {
     std::vector<int> local(sources.size(), -1);
