@@ -2,6 +2,8 @@
 // (ntt.hip), the passes fused with base conversion (ntt_fused.hip) and those that make their own input
 // (sample.hip, encode_gpu.hip).
 #pragma once
+#include <type_traits>
+
 #include "fpmod.h"
 #include "internal.h"
 #include "ks_common.h"
@@ -129,6 +131,29 @@ struct PassGeo {
   static constexpr int LDS_WORDS = COLS * (C + TPC);
 };
 
+// f(integral_constant<int, i>) for i in [A, B).  A 512-point pass's stages are too much code for the
+// compiler to unroll a loop over them, and a loop's elements and twiddles would lie in memory (784 bytes a
+// lane; an integer transform of 8 limbs at N = 2^17 took 70 us that way, 23 us in registers).
+template <int A, int B, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (A < B) {
+    f(std::integral_constant<int, A>{});
+    static_for<A + 1, B>(f);
+  }
+}
+// groups that a thread's contiguous points touch at stage st (of those narrower than a thread's points), and
+// at the stages from a to b
+template <class G>
+__device__ __forceinline__ constexpr int stage_groups(int st) {
+  return G::EPT / (2 * (G::C >> (st + 1))) > 0 ? G::EPT / (2 * (G::C >> (st + 1))) : 1;
+}
+template <class G>
+__device__ __forceinline__ constexpr int stage_groups(int a, int b) {
+  int n = 0;
+  for (int st = a; st < b; ++st) n += stage_groups<G>(st);
+  return n;
+}
+
 // Row passes of one wave per workgroup: row_cols chunks of C words, so a barrier costs nothing.
 template <int LOGC>
 constexpr int row_cols() {
@@ -206,9 +231,8 @@ __device__ __forceinline__ void fwd_core(uint64_t (&x)[E], uint64_t* s,
         w[(1 << st) + i - 1] = twv(k);
         ws[(1 << st) + i - 1] = tws(k);
       }
-#pragma unroll
-    for (int st = 0; st < LE; ++st) {
-      const int tu = EPT >> (st + 1);
+    static_for<0, LE>([&](auto stage) {
+      constexpr int st = stage, tu = EPT >> (st + 1);
 #pragma unroll
       for (int u = 0; u < EPT; ++u)
         if ((u & tu) == 0) {
@@ -216,7 +240,7 @@ __device__ __forceinline__ void fwd_core(uint64_t (&x)[E], uint64_t* s,
           bfly_fwd<FP>(x[u], x[u + tu], w[(1 << st) + i - 1], ws[(1 << st) + i - 1], t.c, t.qd, t.qinv,
                        red_fwd(st, LOGC));
         }
-    }
+    });
   }
   // transpose to the contiguous layout
 #pragma unroll
@@ -240,19 +264,15 @@ __device__ __forceinline__ void fwd_core(uint64_t (&x)[E], uint64_t* s,
         ++pos;
       }
     }
-    pos = 0;
-#pragma unroll
-    for (int st = LE; st < LOGC; ++st) {
-      const int d = C >> (st + 1);
-      const int ng = EPT / (2 * d) > 0 ? EPT / (2 * d) : 1;
+    static_for<LE, LOGC>([&](auto stage) {
+      constexpr int st = stage, d = C >> (st + 1), first = stage_groups<G>(LE, st);
 #pragma unroll
       for (int v = 0; v < EPT; ++v)
         if ((v & d) == 0) {
-          const int gi = v / (2 * d);
-          bfly_fwd<FP>(x[v], x[v + d], w[pos + gi], ws[pos + gi], t.c, t.qd, t.qinv, red_fwd(st, LOGC));
+          const int g = first + v / (2 * d);
+          bfly_fwd<FP>(x[v], x[v + d], w[g], ws[g], t.c, t.qd, t.qinv, red_fwd(st, LOGC));
         }
-      pos += ng;
-    }
+    });
   }
 }
 
@@ -282,19 +302,15 @@ __device__ __forceinline__ void inv_core(uint64_t (&x)[E], uint64_t* s,
         ++pos;
       }
     }
-    pos = 0;
-#pragma unroll
-    for (int st = LOGC - 1; st >= LE; --st) {
-      const int d = C >> (st + 1);
-      const int ng = EPT / (2 * d) > 0 ? EPT / (2 * d) : 1;
+    static_for<0, LOGC - LE>([&](auto stage) {
+      constexpr int st = LOGC - 1 - stage, d = C >> (st + 1), first = stage_groups<G>(st + 1, LOGC);
 #pragma unroll
       for (int v = 0; v < EPT; ++v)
         if ((v & d) == 0) {
-          const int gi = v / (2 * d);
-          bfly_inv<FP>(x[v], x[v + d], w[pos + gi], ws[pos + gi], t.c, t.qd, t.qinv, red_inv(st, LOGC));
+          const int g = first + v / (2 * d);
+          bfly_inv<FP>(x[v], x[v + d], w[g], ws[g], t.c, t.qd, t.qinv, red_inv(st, LOGC));
         }
-      pos += ng;
-    }
+    });
   }
   // transpose to the strided layout
 #pragma unroll
@@ -313,9 +329,8 @@ __device__ __forceinline__ void inv_core(uint64_t (&x)[E], uint64_t* s,
         w[(1 << st) + i - 1] = twv(k);
         ws[(1 << st) + i - 1] = tws(k);
       }
-#pragma unroll
-    for (int st = LE - 1; st >= 0; --st) {
-      const int tu = EPT >> (st + 1);
+    static_for<0, LE>([&](auto stage) {
+      constexpr int st = LE - 1 - stage, tu = EPT >> (st + 1);
 #pragma unroll
       for (int u = 0; u < EPT; ++u)
         if ((u & tu) == 0) {
@@ -323,7 +338,7 @@ __device__ __forceinline__ void inv_core(uint64_t (&x)[E], uint64_t* s,
           bfly_inv<FP>(x[u], x[u + tu], w[(1 << st) + i - 1], ws[(1 << st) + i - 1], t.c, t.qd, t.qinv,
                        red_inv(st, LOGC));
         }
-    }
+    });
   }
 }
 
