@@ -831,6 +831,25 @@ static size_t uniform_jobs(const std::vector<KSJob>& jobs, int n_grp, size_t n_s
   return most;
 }
 
+// Whether the sums of n_grp outputs with n_src sources each are faster with the list's products shared
+// (k_keymac_uniform) than output by output (k_keymac_masked).  Making the products takes nd ext N / 64 rounds of
+// 2 nd + 1 words a rotation, whatever the number of outputs, and a workgroup's sixteen waves take an output each: so
+// where there are many rounds it needs outputs to share them, and where there are few the launch is short either
+// way and the saved passes count.  Both sides with ModUp and ModDown (us; shared, by output), rotations from one source:
+//   N = 2^14, 7 limbs, 49 rotations: 5 outputs 783, 577; 10 955, 918; 12 992, 1044; 16 1081, 1320; 48 2316, 3723
+//   N = 2^16, 7 limbs, 49: 5 outputs 3020, 1804; 8 3302, 2735; 16 4082, 5148
+//   N = 2^13, 16 limbs, 48: 5 outputs 1265, 858; 12 1588, 1627
+//   2304 rounds (N = 2^12, 7 limbs, 25): 5 outputs 183, 181; 8 197, 205; 1536 rounds (N = 2^13, 3 limbs, 48):
+//   5 outputs 208, 228; 3072 rounds (N = 2^14, 3 limbs, 49): 5 outputs 340, 281; 10 416, 411; 12 440, 474
+// Where every rotation has a source of its own (giant steps) each wave reads its output's digits alone, from all
+// over memory: N = 2^14, 7 limbs, 114 of them: 5 outputs 4739, 3770; 16 16168, 12257; 32 30449, 23885; N = 2^13,
+// 7 limbs, 77: 16 outputs 4396, 4077.  A ring of 2^12 has its digits in cache: 16 limbs, 7 of them: 16 outputs 744,
+// 772; N = 2^11, 3 limbs, 24: 5 outputs 136, 170.
+static bool uniform_pays(const ckks_ctx* c, int nd, int ext, int n_grp, size_t n_src) {
+  const size_t rounds = (size_t)nd * ext * c->N / 64;
+  return (n_src == 1 || c->log_n <= 12) && (rounds <= 2304 || n_grp >= 12);
+}
+
 // The masked sums of outputs that share their list: A [n_grp][2][ext][N], first polynomials included
 static void masked_uniform(ckks_ctx* c, int level, const std::vector<const uint64_t*>& sources,
                            const std::vector<KSJob>& jobs, int n_grp, uint64_t* A) {
@@ -935,7 +954,7 @@ void keyswitch_masked_sum(ckks_ctx* c, int level, const std::vector<const uint64
   // an output's sources lie in one chunk there, so they have to fit it (giant steps bring one a rotation: 140
   // of them at N = 2^16 and 16 limbs are 11.7 GB)
   const size_t n_src = fused_basis(c) && !by_key && nd <= KR_MAXD ? uniform_jobs(jobs, n_grp, sources.size()) : 0;
-  if (n_src == 1 || (n_src && n_src * per_src <= KS_BUDGET)) {
+  if (n_src && uniform_pays(c, nd, ext, n_grp, n_src) && (n_src == 1 || n_src * per_src <= KS_BUDGET)) {
     masked_uniform(c, level, sources, jobs, n_grp, A);
     std::vector<FinalJob> finals;
     for (uint64_t* o : outs) finals.push_back(FinalJob{o, nullptr, nullptr, 1, accumulate ? 1 : 0, 0});
