@@ -99,3 +99,54 @@ def test_lines_between_shared_and_separate_products(log_n, family, f_out, n_q, n
     words = 2 * (d["level_out"] + 1) * ctx.N
     for a, b in zip(*outs):
         assert torch.equal(a.reshape(-1)[:words], b.reshape(-1)[:words])
+
+
+def _shift_layer(fg, graph, log_n, f_out, shifts, n_q=3, q_bits=50):
+    """A baby-step/giant-step layer whose nodes' neighbours are exactly the given shifts away, uniform masks and inputs,
+    and its outputs by the per-operation form."""
+    import torch
+    ctx = fg.Context(log_n, n_q, q_bits, 1, 60)
+    rng = np.random.default_rng(1)
+    nbrs = [[] for _ in range(ctx.M)]
+    for v, s in zip(rng.integers(0, ctx.M, len(shifts)), shifts):
+        nbrs[v].append((v + int(s)) % ctx.M)
+    plan = fg.Plan(ctx, *graph.normalize(ctx.M, [np.unique(x).astype(int) for x in nbrs], "mean"), ctx.M, [2, f_out],
+                   [rng.normal(0, 0.1, (2, f_out))], first_mode=1, use_noo=False, family=2, t=1)
+    d = plan.ficgcn_plan_info()[0]
+    _, ev = ctx.ckks_keygen(3, plan.ficgcn_plan_rot_steps(), with_relin=False)
+    plan.ficgcn_plan_fill_operands(4)
+    x = torch.empty((2, 2, d["level_in"] + 1, ctx.N), dtype=torch.int64, device="cuda")
+    for i, q in enumerate(ctx.ckks_ctx_moduli()[: d["level_in"] + 1]):
+        x[:, :, i].random_(0, q, generator=torch.Generator(device="cuda").manual_seed(9 + i))
+    words = 2 * (d["level_out"] + 1) * ctx.N
+
+    def run(mode):
+        outs = [ctx.ct_buffer(d["level_in"]) for _ in range(f_out)]
+        plan.ficgcn_gcn_layer(ev, 0, list(x), outs, mode=mode)
+        return [o.reshape(-1)[:words] for o in outs]
+    return ctx, d, run, run(0)
+
+
+@pytest.mark.parametrize("case", ["two lists of terms", "a short rest", "more ciphertexts than the table"])
+def test_sums_over_several_launches(case):
+    """Three ciphertexts: the term list holds 12288 terms and the ciphertext table 128 places a launch.  What is left
+    goes to a second launch, or, below 3000 terms, to the sums that read ciphertexts from memory."""
+    import torch
+    from paper_2506_10399_amd import ficgcn as fg, graph
+    rng = np.random.default_rng(7)
+    if case == "more ciphertexts than the table":
+        # giant steps of 256; the first forty of them share 128 baby steps, the others take any
+        log_n, n_shifts, G = 17, 4649, 256   # the identity is not among those drawn
+        shifts = np.concatenate([256 * g + (rng.permutation(128)[:100] if 128 <= g < 168 else rng.permutation(256)[:3])
+                                 for g in range(256)])
+    else:
+        log_n, G, n_shifts = 15, 128, 15800 if case == "two lists of terms" else 13000
+        shifts = rng.permutation(1 << 14)[:n_shifts]
+    ctx, d, run, want = _shift_layer(fg, graph, log_n, 3, shifts)
+    assert (d["G"], d["n_shifts"]) == (G, n_shifts)
+    ctx.ficgcn_profile_enable(True)
+    got = run(1)
+    assert ctx.ficgcn_profile_read("bsgs_inner")[1] == 2
+    ctx.ficgcn_profile_enable(False)
+    for a, b in zip(want, got):
+        assert torch.equal(a, b)
