@@ -44,14 +44,16 @@ __device__ __forceinline__ double fmulmod(double a, double b, double q, double q
   return r < 0.0 ? r + q : r;
 }
 
-// signed product: a in (-q, q), b in [0, q) -> (-q, q)
+// signed product: a an integer in (-c q, c q), c at most 8, b in [0, q) -> within (1/2 + 3c/8) q of 0: the
+// quotient is below c q, so its estimate is off by at most c/4 and the low part of the product is below c/8 of q
+// (c = 1: 7/8; ntt_dev.h counts the transforms' stages); hi - qt q is an integer below 2^53, so the fma is exact
 __device__ __forceinline__ double fmulmod_s(double a, double b, double q, double qinv) {
   const double hi = a * b;
   const double lo = fma(a, b, -hi);
   const double qt = rint(hi * qinv);
   return fma(-qt, q, hi) + lo;
 }
-// t in (-2q, 2q) -> (-q, q), congruent
+// t an integer that a double holds, t / q within 2^20 of 0 -> congruent, within (1/2 + 2^-31) q + 1 of 0
 __device__ __forceinline__ double sred(double t, double q, double qinv) { return fma(-rint(t * qinv), q, t); }
 // (-q, q) -> [0, q)
 __device__ __forceinline__ double canon(double r, double q) { return r < 0.0 ? r + q : r; }

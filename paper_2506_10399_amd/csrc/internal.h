@@ -133,7 +133,9 @@ struct ckks_ctx {
   std::vector<uint64_t> h_psi, h_psi_s, h_ipsi, h_ipsi_s, h_ninv, h_ninv_s;   // host tables
   std::vector<ficgcn::Mod> h_mods;
   bool on_device = false;
-  int ntt_cols[2] = {16, 4};          // NTT workgroup width (column pass, row pass); autotuned
+  // NTT workgroup width (column pass, row pass), autotuned on the plain passes; the column passes that make or
+  // convert their input have widths of their own
+  int ntt_cols[2] = {16, 4};
   int ntt_split = 0;                  // log2 of the column pass's transform size (0: log_n / 2); autotuned
   hipStream_t stream = nullptr;
   int device = 0;

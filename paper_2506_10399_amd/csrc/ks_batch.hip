@@ -5,7 +5,9 @@
 // is hoisted on its ModUp; U = R when each ciphertext is switched once, as
 // for relinearising a layer).  Each stage is one launch over the batch:
 //   ModUp  : inverse NTT of the U sources, fast base conversion of every
-//            digit of every source, forward NTT of the extended limbs;
+//            digit of every source, forward NTT of the extended limbs (for one or
+//            two special primes the conversion runs inside the transforms' column
+//            passes, ntt_fused.hip; the same for ModDown and the rescales);
 //   inner  : acc_r = sum_d sigma_{g_r}(D_{src(r),d}) * key_{r,d}   (both components);
 //   ModDown: inverse NTT of the P limbs of every acc_r, rounded conversion
 //            to Q_l, forward NTT, then the grouped final step
@@ -1152,10 +1154,7 @@ void rescale_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
 // limbs instead of l + (l - 1).  h_k = floor(q_k / 2).
 constexpr int RS2_MAX = 32;
 struct RSK2 {
-  uint64_t h1[RS2_MAX], h2[RS2_MAX];            // floor(q_l / 2), floor(q_{l-1} / 2) mod q_i
-  uint64_t inv1[RS2_MAX], inv1_s[RS2_MAX];      // q_l^-1 mod q_i, Shoup
-  uint64_t inv2[RS2_MAX], inv2_s[RS2_MAX];      // q_{l-1}^-1 mod q_i
-  uint64_t inv12[RS2_MAX], inv12_s[RS2_MAX];    // (q_l q_{l-1})^-1 mod q_i
+  uint64_t inv12[RS2_MAX], inv12_s[RS2_MAX];    // (q_l q_{l-1})^-1 mod q_i, Shoup
 };
 
 // c''_i = c_i (q_l q_{l-1})^-1 + f_i, compacted in place from [2][l+1][N] to
@@ -1191,18 +1190,10 @@ void rescale2_batch(ckks_ctx* c, int level, const std::vector<uint64_t*>& cts) {
   uint64_t* f = (uint64_t*)dev_scratch(c, S_RS_D, (size_t)2 * n * (level - 1) * N * 8);
   RSK2 k{};
   const RSK &r1 = c->rsk[level], &r2 = c->rsk[level - 1];
-  for (int i = 0; i < level; ++i) {
+  for (int i = 0; i < level - 1; ++i) {
     const uint64_t q = c->mod[i];
-    k.h1[i] = r1.h[i];
-    k.inv1[i] = r1.inv[i];
-    k.inv1_s[i] = r1.inv_s[i];
-    if (i < level - 1) {
-      k.h2[i] = r2.h[i];
-      k.inv2[i] = r2.inv[i];
-      k.inv2_s[i] = r2.inv_s[i];
-      k.inv12[i] = (uint64_t)((u128)k.inv1[i] * k.inv2[i] % q);
-      k.inv12_s[i] = shoup(k.inv12[i], q);
-    }
+    k.inv12[i] = (uint64_t)((u128)r1.inv[i] * r2.inv[i] % q);
+    k.inv12_s[i] = shoup(k.inv12[i], q);
   }
   rescale2_prep(c, level, cd, n, last, f);
   hipLaunchKernelGGL(k_rs2_final, dim3(N / KB, 2 * n), dim3(KB), 0, c->stream, cd, f, level, k, c->log_n, c->t.mods);

@@ -34,12 +34,6 @@ FICGCN_FD uint64_t mul_shoup(uint64_t a, uint64_t w, uint64_t ws, uint64_t q) {
   return r >= q ? r - q : r;
 }
 
-// Shoup without the final correction: result in [0, 2q) (butterfly-internal use)
-FICGCN_FD uint64_t mul_shoup_lazy(uint64_t a, uint64_t w, uint64_t ws, uint64_t q) {
-  uint64_t h = mulhi64(a, ws);
-  return a * w - h * q;
-}
-
 struct Mod {
   uint64_t q;
   uint64_t r_hi, r_lo;   // floor(2^128 / q)

@@ -5,15 +5,15 @@
 namespace ficgcn {
 
 // ModUp and ModDown go through the fused kernels for one or two special primes (every shipped
-// configuration): a thread holds 16 coefficients of each of a digit's limbs, and its sums of lazy
-// products stay below 8q.  Longer digits take the separate passes.
+// configuration): a thread holds eight coefficients of each of a digit's limbs, the tables have room for
+// two sources a digit, and a sum of two lazy products stays below 8q.  Longer digits take the separate passes.
 inline bool fused_basis(const ckks_ctx* c) { return c->alpha <= 2; }
 // ModUp of U polynomials [l1][N] in evaluation form, poly u at srcs[u] (device table) or, when
 // srcs is null, at `one` (U = 1): D [U][nd][ext][N].  tmp: U * l1 limbs.
 void modup_polys(ckks_ctx* c, int level, const uint64_t* const* srcs, const uint64_t* one, int U, uint64_t* tmp,
                  uint64_t* D);
 // ModDown's conversion of Z accumulators [ext][N] (poly z at acc + z * ext * N; their P limbs are
-// left in coefficient form): conv [Z][l1][N].  The transform of conv stops before its row pass
+// left half transformed, after the inverse row pass): conv [Z][l1][N].  The transform of conv stops before its row pass
 // when `rows` is false (a row pass with a fused final step follows).
 void moddown_polys(ckks_ctx* c, int level, uint64_t* acc, int Z, uint64_t* conv, bool rows);
 // One final step per ciphertext on ModDown's conversion before its row pass (moddown_polys with
