@@ -805,8 +805,8 @@ def keyswitch_bench(args):
     ciphertexts in one batch, and 16 relinearised squares, one call each.  Reported per form: key switches
     per second, the algorithmic bytes per switch (source and output
     ciphertexts, key; the hoisted form's shared ModUp input counted once)
-    and the bytes every pass of the launch sequence moves (NTT passes, base
-    conversions, inner products), as rates."""
+    and the bytes every pass of the launch sequence moves (row passes, column
+    passes with the base conversions between them, inner products), as rates."""
     import torch
     from paper_2506_10399_amd import ficgcn as fg
     torch.cuda.set_device(0)
@@ -830,11 +830,13 @@ def keyswitch_bench(args):
         key_b = limb * 2 * beta * ext
         alg = dict(hoisted=(key_b + 2 * L1 * limb) + 2 * L1 * limb / len(steps),   # key + output, source shared
                    batch=key_b + 4 * L1 * limb, relin=key_b + 4 * L1 * limb)
-        modup = limb * (4 * L1 + 5 * beta * ext)
+        # row pass of the sources (and their copy into the digits), column passes with the conversion, row pass
+        modup = limb * (L1 + 3 * beta * ext)
         inner = limb * (3 * beta * ext + 2 * ext)
-        moddown = limb * (10 * a + 17 * L1)
+        # row pass of the P limbs, column passes with the conversion, row pass with the last step
+        moddown = limb * (6 * a + 9 * L1)
         passes = dict(hoisted=inner + moddown + modup / len(steps), batch=modup + inner + moddown,
-                      relin=modup + inner + moddown + limb * 7 * L1)
+                      relin=modup + inner + moddown + limb * 8 * L1)
         forms = dict(
             hoisted=lambda: ctx.ckks_rotate_hoisted(ev, xs[0], lv, steps, outs),
             batch=lambda: ctx.ckks_rotate_batch(ev, xs[1:], lv, steps, outs),
@@ -1049,21 +1051,19 @@ def radix2_bench(args):
     # the layer's inputs as the first layer leaves them: squared (scale Delta^2,
     # rescale pending), one column per ciphertext in the plan's node order
     rng = np.random.default_rng(3)
-    pi = plans["bsgs"].ficgcn_plan_node_order()
-    for p in plans.values():
-        assert np.array_equal(p.ficgcn_plan_node_order(), pi)
     z = rng.uniform(-1, 1, (w.graph.n, d1["f_in"]))
-    rows = np.zeros((d1["f_in"], N // 2))
-    rows[:, pi] = z.T
-    pts = ctx.ckks_encode_batch(rows, 2.0 ** prm["log_scale"], lv_in)
-    ins = []
-    for i in range(d1["f_in"]):
-        c = ctx.ckks_encrypt(cl, pts[i], lv_in, 99, i)
-        ins.append(ctx.ckks_mul_relin(ev, c, c, lv_in))
     ref = fp64_gcn(rp, col, val, z * z, [w.weights[1]])
     res = {}
     for k, p in plans.items():
         d = p.ficgcn_plan_info()[1]
+        pi = p.ficgcn_plan_node_order()   # the radix-2 routing has an order of its own
+        rows = np.zeros((d1["f_in"], N // 2))
+        rows[:, pi] = z.T
+        pts = ctx.ckks_encode_batch(rows, 2.0 ** prm["log_scale"], lv_in)
+        ins = []
+        for i in range(d1["f_in"]):
+            c = ctx.ckks_encrypt(cl, pts[i], lv_in, 99, i)
+            ins.append(ctx.ckks_mul_relin(ev, c, c, lv_in))
         p.ficgcn_plan_encode()
         outs = [ctx.ct_buffer(lv_in) for _ in range(d["n_out_cts"])]
         p.ficgcn_gcn_layer(ev, 1, ins, outs, mode=2)
