@@ -549,7 +549,7 @@ static void src_cols(ckks_ctx* c, uint64_t* out, size_t stride, const S& src, in
   else                  \
     Y(LC, MID_COLS)
   switch (lc) {
-    case 4: Y(4, MID_COLS); break;
+    case 4: Y(4, 2 * MID_COLS); break;   // two threads a column: 32 of them are a wave
     case 5: Y(5, MID_COLS); break;
     case 6: X(6); break;
     case 7: X(7); break;
